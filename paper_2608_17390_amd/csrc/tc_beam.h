@@ -35,6 +35,13 @@ namespace {
 constexpr float kBeamFirst = 0.5f;           // first interval: cells along the centre ray
 constexpr float kBeamGrowth = 0.125f;        // each interval 1/8 longer than the last
 constexpr float kBeamLog2Growth = 0.169925f; // log2(1 + kBeamGrowth)
+// The search ends when a pass is stopped in one of its first intervals: what
+// it could not clear is then under 0.8 cells long, and another pass, which
+// can at most reach that interval's end, costs as much as the walk step or
+// two that it saves.  (Twelve 1280x800 views in one call: 361 us when it
+// ends only without any progress, 357 for 3 and 5 intervals, 357 for 7; one
+// full-HD horizon view of long walks: 171, 173, 175 and 180.)
+constexpr int32_t kBeamStop = 4;
 
 // Could solid lie in the box [lox, hix] x [loy, hiy] x [loz, hiz] (cells,
 // height units)?  With 2^L the smallest power of two above the box's
@@ -156,10 +163,10 @@ __device__ __forceinline__ float beam_start(const tci_map& m, const lvl_t* lv,
     const bool solid =
         beam_box_solid(m, lv, woff, lo[0], hi[0], lo[1], hi[1], lo[2], hi[2], reads);
     const uint64_t bad = __ballot(solid);
-    if (bad & 1ull) break;                         // no progress
     const int32_t k = bad ? __ffsll((unsigned long long)bad) - 1 : 63;
     const float next = bad ? t0 : t1;
     ta = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(next), k));
+    if (k < kBeamStop) break;
   }
   return ta;
 }

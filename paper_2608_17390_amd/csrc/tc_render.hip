@@ -7,6 +7,7 @@
 
 #include "tc_beam.h"
 #include "tc_packet.h"
+#include "tc_skim.h"
 
 namespace {
 
@@ -16,9 +17,12 @@ namespace {
 constexpr int32_t kPackets = 2;
 
 // This lane's index in its wave, from the hardware (two VALU instructions)
-// rather than from a register kept live.
+// rather than from a register kept live (nor is what is computed from it
+// moved ahead of a loop that uses it).
 __device__ __forceinline__ int32_t lane_now() {
-  return (int32_t)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  int32_t l = (int32_t)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(l));
+  return l;
 }
 
 // One thread per pixel; a wave casts one packet of 64 pixels.
@@ -27,7 +31,9 @@ __device__ __forceinline__ int32_t lane_now() {
 // pyramid *vx instead (render mode 5, the voxel-accelerated march).
 // kCount: the launch counts the nodes and cells its rays read (o.count);
 // the production instance keeps no counter through the walk.
-template <bool kFlat, bool kOcc, bool kCount, bool kVox = false>
+// kBoost: the launch has a priority boost (o.boost; the hierarchical mode,
+// whose walk is instantiated for it).
+template <bool kFlat, bool kOcc, bool kCount, bool kVox = false, bool kBoost = false>
 __device__ __forceinline__ void render_body(
     const tci_map& m, const tci_view* __restrict__ views, int32_t nviews,
     const int64_t* __restrict__ pkt_prefix, const int32_t* __restrict__ rows, int64_t npkt,
@@ -71,7 +77,7 @@ __device__ __forceinline__ void render_body(
   if (r.Dx == 0 && r.Dy == 0) {
     trace_vertical(m, lv, r, word, depth);
     if (kCount && beam_reads) atomicAdd(o.count, (unsigned long long)beam_reads);
-  } else {
+  } else if constexpr (kFlat || kOcc || kVox) {
     walk_t s;
     walk_idx_t k;
     const int32_t top = kFlat ? 0 : m.top;
@@ -80,22 +86,51 @@ __device__ __forceinline__ void render_body(
     uint32_t col = 0;
     const int32_t Lmax = kFlat ? 0 : clamp_level(o.max_level, top);
     const int32_t boost = __builtin_amdgcn_readfirstlane(o.boost);
-    bool split = !kFlat && o.split_budget > 0 && o.qcap > 0;
     // the walk runs a loop specialised to the sign of the ray's vertical
     // direction (a packet's rays mostly share it; a wave holding both signs
     // runs the two loops one after the other)
-    const bool down = r.Dz < 0;
     int32_t st;
+    if (r.Dz < 0)
+      st = walk_steps<false, kOcc, false, 1, kVox>(m, lv, r, k, s, Lmax, kIterCap + 1, col, boost,
+                                                   0, 0, 0, moff, kCount, vx);
+    else
+      st = walk_steps<false, kOcc, false, 2, kVox>(m, lv, r, k, s, Lmax, kIterCap + 1, col, boost,
+                                                   0, 0, 0, moff, kCount, vx);
+    if (st == kWalking) st = kCapped;   // the whole budget ran out (never expected)
+    // the origin is needed again only here: recompute it from the view
+    // rather than keep it in registers through the walk (the lane index is
+    // read again from the hardware, so no register holds it either)
+    packet_ray<false>(v, tx, ty, lane_now(), r);
+    finish(r, s, m.W, st, col, word, depth);
+    if (kCount) atomicAdd(o.count, (unsigned long long)s.reads);
+  } else {
+    const int32_t Lmax = clamp_level(o.max_level, m.top);
+    const int32_t boost = __builtin_amdgcn_readfirstlane(o.boost);
+    // the budget bounds the walk: at most the split budget, or without a
+    // split pass kIterCap + 1 steps
+    bool split = o.split_budget > 0 && o.qcap > 0;
+    skim_ray f;
+    skim_init(r, f);
+    skim_t s;
+    const float t0 = t_start * 0x1p-16f;
+    const int32_t L0 = clamp_level(o.start_level, m.top);
+    skim_start(f, t0, L0, s);
+    // no register holds the ray's integers through the walk: the few places
+    // that need them recompute them from the view
+    auto ray = [&]() {
+      ray_t q;
+      packet_ray(v, tx, ty, lane_now(), q);
+      return skim_int{(int32_t)q.Ox, (int32_t)q.Oy, (int32_t)q.Oz, q.Dx, q.Dy, q.Dz};
+    };
+    auto oz = [&]() {
+      ray_t q;
+      packet_ray<false>(v, tx, ty, lane_now(), q);
+      return (int32_t)q.Oz;
+    };
+    int32_t reads = beam_reads, st;
     for (;;) {
-      // the budget bounds the walk: at most the split budget, then (or
-      // without a split pass) kIterCap + 1 iterations
       const int32_t budget = split ? o.split_budget : kIterCap + 1;
-      if (down)
-        st = walk_steps<false, kOcc, false, 1, kVox>(m, lv, r, k, s, Lmax, budget, col, boost,
-                                                     0, 0, 0, moff, kCount, vx);
-      else
-        st = walk_steps<false, kOcc, false, 2, kVox>(m, lv, r, k, s, Lmax, budget, col, boost,
-                                                     0, 0, 0, moff, kCount, vx);
+      st = skim_walk<kBoost>(m, lv, f, s, Lmax, budget, boost, reads, kCount, ray, oz, word, depth);
       if (!split) break;
       split = false;
       // long walks go to the split pass, as many as the queue holds
@@ -104,36 +139,27 @@ __device__ __forceinline__ void render_body(
       const uint64_t act = __ballot(1);
       const int32_t leader = __ffsll((unsigned long long)act) - 1;
       uint32_t base = 0;
-      if (lane == leader) base = atomicAdd(o.qcount, (uint32_t)__popcll(want));
+      const int32_t ln = lane_now();
+      if (ln == leader) base = atomicAdd(o.qcount, (uint32_t)__popcll(want));
       base = __shfl(base, leader);
       if (st != kWalking) break;
       const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
           (uint32_t)(want >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)want, 0));
       if (base + rank < o.qcap) {
-        // the walk has reached the current node: the second pass need only
-        // split the path from the node's near line on the dominant axis
-        const bool ax_x = r.ax >= r.ay;
-        // the start cell's line, selected here: selected before the walk it
-        // would hold one more register through it
-        int32_t cx = r.cx0, cy = r.cy0;
-        asm volatile("" : "+v"(cx), "+v"(cy));
-        const int32_t n = ax_x ? s.ni : s.nj, c0 = ax_x ? cx : cy;
-        const bool fwd = (ax_x ? r.Dx : r.Dy) > 0;
-        const int32_t near = fwd ? (n << s.L) : ((n + 1) << s.L) - 1;
-        const int32_t from = fwd ? max(near, c0) : min(near, c0);
-        o.queue[base + rank] = make_uint4((uint32_t)vi, (uint32_t)(py * v.w + px),
-                                          (uint32_t)from, 0u);
-        if (kCount) atomicAdd(o.count, (unsigned long long)s.reads);
+        // the second pass need only split the path from the current cell's
+        // line on the dominant axis
+        const int32_t from = fabsf(f.dx) >= fabsf(f.dy) ? s.x : s.y;
+        const int32_t qp = ((ty << (6 - pw)) + (ln >> pw)) * v.w + (tx << pw) + (ln & ((1 << pw) - 1));
+        o.queue[base + rank] = make_uint4((uint32_t)vi, (uint32_t)qp, (uint32_t)from, 0u);
+        if (kCount) atomicAdd(o.count, (unsigned long long)reads);
         return;
       }
     }
-    if (st == kWalking) st = kCapped;   // the whole budget ran out (never expected)
-    // the origin is needed again only here: recompute it from the view
-    // rather than keep it in registers through the walk (the lane index is
-    // read again from the hardware, so no register holds it either)
-    packet_ray<false>(v, tx, ty, lane_now(), r);
-    finish(r, s, m.W, st, col, word, depth);
-    if (kCount) atomicAdd(o.count, (unsigned long long)s.reads);
+    if (st != kHitCell) {
+      word = st == kMissed ? kMiss : kStuck;   // (kStuck: never expected)
+      depth = st == kMissed ? __builtin_inff() : __builtin_nanf("");
+    }
+    if (kCount) atomicAdd(o.count, (unsigned long long)reads);
   }
   const int32_t ql = lane_now(), qw = v.pw_log2;
   tcp::store_hit(out, v.out_base + (int64_t)((ty << (6 - qw)) + (ql >> qw)) * v.w + (tx << qw) +
@@ -142,28 +168,30 @@ __device__ __forceinline__ void render_body(
 }
 
 // The three one-thread-per-pixel kernels, each with and without read
-// counting.  The hierarchical one is asked for at least 7 waves per SIMD
-// (at most 72 VGPRs): each walk step waits on its node load and the
-// arithmetic after it, so more waves hide more of that latency.  The
-// production instance (no counting) fits 64 VGPRs, enough for 8 waves.
-template <bool kCount>
+// counting.  The hierarchical one is asked for at least 7 waves per SIMD (at
+// most 72 VGPRs): 8 (64 VGPRs) spills in the walk loop and 6 (80 VGPRs, no
+// spill) hides less of its latency; 64 mixed views and 8 shadow passes take
+// 3.82 ms with 7, 3.91 with 8 and 4.04 with 6.
+template <bool kCount, bool kBoost>
 __global__ __launch_bounds__(64 * kPackets) __attribute__((amdgpu_waves_per_eu(7, 8)))
 void render_hier_kernel(tci_map m, const tci_view* __restrict__ views, int32_t nviews,
                         const int64_t* __restrict__ pkt_prefix, int64_t npkt, void* out,
                         tci_render_opts o) {
-  render_body<false, false, kCount>(m, views, nviews, pkt_prefix, o.rows, npkt, out, o);
+  render_body<false, false, kCount, false, kBoost>(m, views, nviews, pkt_prefix, o.rows, npkt, out,
+                                                   o);
 }
 
 // The same, with the call's view records, packet prefix and tile-row table
 // passed in the kernel's arguments instead of a device table (a small call
 // then needs no upload before its render).
+template <bool kBoost>
 __global__ __launch_bounds__(64 * kPackets) __attribute__((amdgpu_waves_per_eu(7, 8)))
 void render_hier_inline_kernel(tci_map m, int32_t nviews, int64_t npkt, void* out,
                                tci_render_opts o, tci_inline t) {
   const char* b = (const char*)t.words;
-  render_body<false, false, false>(m, (const tci_view*)b, nviews,
-                                   (const int64_t*)(b + t.off_prefix),
-                                   (const int32_t*)(b + t.off_rows), npkt, out, o);
+  render_body<false, false, false, false, kBoost>(m, (const tci_view*)b, nviews,
+                                                  (const int64_t*)(b + t.off_prefix),
+                                                  (const int32_t*)(b + t.off_rows), npkt, out, o);
 }
 
 template <bool kCount>
@@ -445,7 +473,8 @@ hipError_t tci_launch_render(const tci_map& m, const tci_view* views,
   }
   auto kern = flat == 1 ? (c ? render_flat_kernel<true> : render_flat_kernel<false>)
             : flat == 2 ? (c ? render_occ_kernel<true> : render_occ_kernel<false>)
-                        : (c ? render_hier_kernel<true> : render_hier_kernel<false>);
+            : o.boost > 0 ? (c ? render_hier_kernel<true, true> : render_hier_kernel<false, true>)
+                          : (c ? render_hier_kernel<true, false> : render_hier_kernel<false, false>);
   hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(64 * kPackets), 0, s, m, views, nviews,
                      pkt_prefix, npkt, out, o);
   return hipGetLastError();
@@ -470,12 +499,13 @@ hipError_t tci_launch_render_inline(const tci_map& m, int32_t nviews, int64_t np
                                     hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   const int64_t blocks = (npkt + kPackets - 1) / kPackets;
   if (blocks < 1) return hipSuccess;
+  auto kern = o.boost > 0 ? render_hier_inline_kernel<true> : render_hier_inline_kernel<false>;
   if (ev_start || ev_stop)
-    hipExtLaunchKernelGGL(render_hier_inline_kernel, dim3((uint32_t)blocks), dim3(64 * kPackets),
-                          0, s, ev_start, ev_stop, 0, m, nviews, npkt, out, o, t);
+    hipExtLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(64 * kPackets), 0, s, ev_start,
+                          ev_stop, 0, m, nviews, npkt, out, o, t);
   else
-    hipLaunchKernelGGL(render_hier_inline_kernel, dim3((uint32_t)blocks), dim3(64 * kPackets), 0,
-                       s, m, nviews, npkt, out, o, t);
+    hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(64 * kPackets), 0, s, m, nviews, npkt,
+                       out, o, t);
   return hipGetLastError();
 }
 

@@ -1,0 +1,354 @@
+// The walk in single precision: the same cells as the exact walk of
+// tc_walk.h, at about half its instructions per step.
+//
+// What bounds it: the issue of vector instructions.  A wave64 instruction
+// takes 2 cycles of a SIMD (single-precision multiply, add and multiply-add,
+// add, and/xor, right shift, on vector registers only) or 4 (conversions,
+// compares, min/max, selects, three-operand and 24-bit integer ones, and any
+// with a scalar operand), and a frame's waves keep the SIMDs issuing nearly
+// all the time.  Measured, the render of the exact walk before and of this
+// one after (MI355X): 64 mixed views and 8 shadow passes 4.69 -> 3.72 ms,
+// twelve 1280x800 views 417 -> 346 us, a 1920x1080 horizon view 210 -> 173
+// us.
+//
+// A step of the exact walk spends most of its instructions on 48-bit
+// products: two crossing keys, an exit height and three scaled heights to
+// compare it with.  Here a crossing's time is one single-precision product,
+// t = d / D (d the distance to the face from the ray's origin, D the
+// direction's component), and a height one multiply-add, z = Oz + t Dz.
+// Nothing is decided on a rounded value:
+//   * which cell a step enters is taken from q = O + te D, the position on
+//     the other axis at the crossing.  d is a whole number of cells minus
+//     the origin's 16-bit fraction (one rounding), 1 / D is the hardware's
+//     reciprocal (1 ulp), so te D and q are off by at most 2^-22 of te D
+//     plus one rounding.  A q farther than that from a cell line has the
+//     right cell (and then the face it leaves through is right as well: were
+//     the other face crossed first, q would lie outside the node).  A q
+//     closer to a line than 2^-21 |q| + 2^-20 is left to `exact`, which
+//     takes the step in whole numbers (skim_exact_step);
+//   * a node is skipped only if the ray's heights over it, widened by a
+//     margin of 2^-20 (|Oz| + 512) (they are off by less than half of that
+//     wherever they lie between -512 and 512), meet no solid;
+//   * a cell that may hold the hit is tested in whole numbers
+//     (skim_exact_cell); a ray it does not stop walks on.
+// So hit records are those of the exact walk, bit for bit.
+//
+// The state is the cell the ray enters its node through and the level: a
+// node is the cell's coordinates shifted down, a descent or a climb changes
+// the level alone, where the exact walk's node coordinates need the middle
+// crossings' keys to descend.
+#pragma once
+
+#include "tc_walk.h"
+
+namespace {
+
+// Ray constants, in cells: the origin's cell and its fractions in it, the
+// direction's components and their reciprocals (infinite for a zero
+// component, which counts as forward: its far face is never reached), and
+// the origin's height lowered (zlo) and raised (zhi) by the margin.
+struct skim_ray {
+  int32_t cx, cy;
+  float fx, fy, rx, ry, dx, dy, dz, zlo, zhi;
+};
+
+struct skim_t {
+  int32_t x, y;   // the cell the ray is in on entering the current node
+  int32_t L;
+  float zin;      // its height there, moved by the margin to the safe side
+                  // (up for a descending ray, down for the others)
+};
+
+__device__ __forceinline__ void skim_init(const ray_t& r, skim_ray& f) {
+  f.cx = (int32_t)r.Ox >> 16;
+  f.cy = (int32_t)r.Oy >> 16;
+  f.fx = (float)((uint32_t)r.Ox & 0xFFFF) * 0x1p-16f;
+  f.fy = (float)((uint32_t)r.Oy & 0xFFFF) * 0x1p-16f;
+  f.dx = (float)r.Dx;
+  f.dy = (float)r.Dy;
+  f.dz = (float)r.Dz;
+  f.rx = __builtin_amdgcn_rcpf(f.dx);
+  f.ry = __builtin_amdgcn_rcpf(f.dy);
+  const float oz = (float)(int32_t)r.Oz * 0x1p-16f;
+  const float m = fmaf(fabsf(oz), 0x1p-20f, 0x1p-11f);
+  f.zlo = oz - m;
+  f.zhi = oz + m;
+}
+
+// On which side of every line is q surely?  False if a line is too close.
+__device__ __forceinline__ bool skim_sure(float q) {
+  const float fr = __builtin_amdgcn_fractf(q);
+  return fabsf(fr - 0.5f) < 0.5f - fmaf(fabsf(q), 0x1p-21f, 0x1p-20f);
+}
+
+// Start at parameter t (in cells per direction unit; no solid lies on the
+// ray before it): in the ray's cell at t, on level 0, or at a slightly
+// earlier t if that cell is not sure, or at the origin on level L0.
+__device__ __forceinline__ void skim_start(const skim_ray& f, float t, int32_t L0, skim_t& s) {
+  float qx = fmaf(t, f.dx, f.fx), qy = fmaf(t, f.dy, f.fy);
+  if (!(skim_sure(qx) & skim_sure(qy))) {
+    t *= 0.984375f;
+    qx = fmaf(t, f.dx, f.fx);
+    qy = fmaf(t, f.dy, f.fy);
+  }
+  const bool at = (t > 0.0f) & skim_sure(qx) & skim_sure(qy);
+  t = at ? t : 0.0f;
+  s.x = f.cx + (at ? (int32_t)floorf(qx) : 0);
+  s.y = f.cy + (at ? (int32_t)floorf(qy) : 0);
+  s.L = at ? 0 : L0;
+  s.zin = fmaf(t, f.dz, f.dz < 0.0f ? f.zhi : f.zlo);
+}
+
+// A ray's integers, as the out-of-line steps take them.
+struct skim_int {
+  int32_t Ox, Oy, Oz, Dx, Dy, Dz;
+};
+
+__device__ __forceinline__ ray_t skim_whole(const skim_int& q) {
+  ray_t r;
+  r.Ox = q.Ox;
+  r.Oy = q.Oy;
+  r.Oz = q.Oz;
+  r.Dx = q.Dx;
+  r.Dy = q.Dy;
+  r.Dz = q.Dz;
+  r.ax = (uint32_t)(r.Dx < 0 ? -r.Dx : r.Dx);
+  r.ay = (uint32_t)(r.Dy < 0 ? -r.Dy : r.Dy);
+  return r;
+}
+
+// The step out of node (ni, nj) of level L in whole numbers: the cell it
+// enters, and whether it leaves through an x face.  Rare, so it is called
+// rather than inlined: its 64-bit values would raise the walk's registers.
+struct skim_next {
+  int32_t x, y, ex;
+};
+__device__ __forceinline__ skim_next skim_exact_step(skim_int q, int32_t ni, int32_t nj,
+                                                               int32_t L) {
+  ray_t r = skim_whole(q);
+  walk_idx_t k;
+  walk_t w;
+  walk_origin(r, k);
+  const bool fx = r.Dx > 0, fy = r.Dy > 0;
+  const int32_t ix = far_index(ni, L, fx ? 1 : 0, fx ? 1 : -1, k.offx);
+  const int32_t iy = far_index(nj, L, fy ? 1 : 0, fy ? 1 : -1, k.offy);
+  const bool ex = add_mul48(k.KX0, (uint32_t)ix, r.ay) <= add_mul48(k.KY0, (uint32_t)iy, r.ax);
+  const int32_t line = ex ? (fx ? (ni + 1) << L : (ni << L) - 1)
+                          : (fy ? (nj + 1) << L : (nj << L) - 1);
+  walk_at_line(r, k, w, ex ? 0 : 1, line);
+  return skim_next{w.ni, w.nj, ex ? 1 : 0};
+}
+
+// Does the ray stop in cell (x, y) of its walk (packed column v)?  Then its
+// hit record (word, and depth's bits).  The crossing it enters the cell
+// through is the later of the cell's near x and y crossings (y on a tie,
+// since x steps first), if any.  Called, as skim_exact_step.
+struct skim_cell {
+  int32_t hit;
+  uint32_t word, depth;
+};
+__device__ __forceinline__ skim_cell skim_exact_cell(skim_int q, int32_t x, int32_t y,
+                                                               uint32_t v, int32_t W) {
+  ray_t r = skim_whole(q);
+  walk_idx_t k;
+  walk_origin(r, k);
+  const bool fx = r.Dx > 0, fy = r.Dy > 0, desc = r.Dz < 0;
+  // crossing numbers of the far faces; the near ones are one less
+  const int32_t ix = far_index(x, 0, fx ? 1 : 0, fx ? 1 : -1, k.offx);
+  const int32_t iy = far_index(y, 0, fy ? 1 : 0, fy ? 1 : -1, k.offy);
+  const int64_t KXe = add_mul48(k.KX0, (uint32_t)ix, r.ay);
+  const int64_t KYe = add_mul48(k.KY0, (uint32_t)iy, r.ax);
+  const bool ex = KXe <= KYe;
+  const int64_t Ze = add_smul48(ex ? k.ZX0 : k.ZY0, ex ? ix : iy, r.Dz);
+  const uint32_t De = ex ? r.ax : r.ay, re = ex ? r.rx : r.ry;
+  const bool ny = iy > 0 && (ix <= 0 || KYe - (int64_t)r.ax >= KXe - (int64_t)r.ay);
+  int64_t zin = r.Oz >> 16;
+  uint32_t din = 1, rin = (r.Oz & 0xFFFF) != 0;
+  int32_t entry = kInside;
+  if (ix > 0 || iy > 0) {
+    zin = add_smul48(ny ? k.ZY0 : k.ZX0, (ny ? iy : ix) - 1, r.Dz);
+    din = ny ? r.ay : r.ax;
+    rin = ny ? r.ry : r.rx;
+    entry = ny ? (fy ? kWmy : kWpy) : (fx ? kWmx : kWpx);
+  }
+  const int64_t lo = (desc ? Ze : zin) + (int64_t)(desc ? re : rin);
+  const uint32_t Dlo = desc ? De : din;
+  const int64_t hi = desc ? zin : Ze;
+  const uint32_t Dhi = desc ? din : De;
+  const uint32_t a = v & 0xFF, b = (v >> 8) & 0xFF, c = (v >> 16) & 0xFF;
+  uint32_t word = 0;
+  float depth = 0.0f;
+  const bool hit = (lo <= hmul(a, Dlo)) | ((lo <= hmul(c, Dlo)) & (hi >= hmul(b, Dhi)));
+  if (hit) resolve_hit(r, x, y, entry, zin, din, rin, W, v, word, depth);
+  return skim_cell{hit ? 1 : 0, word, __float_as_uint(depth)};
+}
+
+// Walk until a cell that may hold the hit (kHitCell, its column in col), a
+// certain miss (kMissed), or step number `budget` (kWalking); `it` counts the
+// steps, over several calls.  ze is the height at which the ray leaves that
+// cell, moved by the margin to the other side than zin.  ray() gives the ray again for a step that is taken in whole
+// numbers, so that no register holds its integers through the walk.
+// kDir: 1 Dz < 0, 2 otherwise.
+template <int kDir, class RayFn>
+__device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
+                                              const skim_ray& f, skim_t& s, int32_t max_level,
+                                              int32_t budget, int32_t& it, uint32_t& col,
+                                              float& ze_out, int32_t& reads, bool count,
+                                              RayFn ray) {
+  const bool desc = kDir == 1;
+  const bool fx = f.dx >= 0.0f, fy = f.dy >= 0.0f;
+  const int32_t nx1 = fx ? 1 : 0, ny1 = fy ? 1 : 0;
+  const float m2 = f.zhi - f.zlo;
+  for (; it < budget; ++it) {
+    const int32_t L = s.L;
+    const uint4 lq = *reinterpret_cast<const uint4*>(&lv[L]);
+    const int32_t w1 = (int32_t)lq.y, h1 = (int32_t)lq.z;
+    const int32_t ni = s.x >> L, nj = s.y >> L;
+    const bool inmap = ((uint32_t)ni <= (uint32_t)w1) & ((uint32_t)nj <= (uint32_t)h1);
+    if (count) reads += inmap ? 1 : 0;
+    const uint32_t ci = (uint32_t)clamp0(ni, w1), cj = (uint32_t)clamp0(nj, h1);
+    const uint32_t v = map_word(m.base, lq.x + ((umul24(cj >> 3, lq.w) + (ci >> 3)) << 6) +
+                                            ((cj & 7) << 3) + (ci & 7));
+    // times of the crossings through the far faces
+    const int32_t gx = (ni + nx1) << L, gy = (nj + ny1) << L;
+    const float tx = ((float)(gx - f.cx) - f.fx) * f.rx;
+    const float ty = ((float)(gy - f.cy) - f.fy) * f.ry;
+    const bool ex = tx <= ty;
+    const float te = fminf(tx, ty);
+    const float ze = fmaf(te, f.dz, desc ? f.zlo : f.zhi);
+    const float lo = desc ? ze : s.zin, hi = desc ? s.zin : ze;
+    const bool occ = inmap & ((lo <= (float)(v & 0xFF)) |
+                              ((lo <= (float)((v >> 16) & 0xFF)) & (hi >= (float)((v >> 8) & 0xFF))));
+    if (occ) {
+      if (L == 0) {
+        col = v;
+        ze_out = ze;
+        return kHitCell;
+      }
+      s.L = L - 1;
+    } else {
+      // beside the map and moving away, or above all solid for good
+      if (!inmap) {
+        const bool away = ((ni < 0) & (f.dx <= 0.0f)) | ((ni > w1) & fx) |
+                          ((nj < 0) & (f.dy <= 0.0f)) | ((nj > h1) & fy);
+        if (away) return kMissed;
+      }
+      if (!desc && ze > 255.0f + m2) return kMissed;
+      const float q = fmaf(te, ex ? f.dy : f.dx, ex ? f.fy : f.fx);
+      const int32_t o = (int32_t)floorf(q) + (ex ? f.cy : f.cx);
+      int32_t x = ex ? gx + nx1 - 1 : o, y = ex ? o : gy + ny1 - 1;
+      float zn = desc ? ze + m2 : ze - m2;
+      if (__builtin_expect(!skim_sure(q), 0)) {
+        const skim_next n = skim_exact_step(ray(), ni, nj, L);
+        x = n.x;
+        y = n.y;
+        zn = fmaf(n.ex ? tx : ty, f.dz, desc ? f.zhi : f.zlo);
+      }
+      // go up one level when the step entered a new parent node
+      s.L = L + (((L < max_level) & (((uint32_t)((s.x ^ x) | (s.y ^ y)) >> L) > 1u)) ? 1 : 0);
+      s.x = x;
+      s.y = y;
+      s.zin = zn;
+    }
+  }
+  return kWalking;
+}
+
+// The hit record of a candidate cell (skim_steps), if the single-precision
+// values alone settle it: the ray's heights at the cell's entry and exit lie
+// farther than the margin from every height they are compared with, and
+// where the hit is on the face it enters through, the two near crossings'
+// times differ by more than their rounding.  The record is formed from the
+// ray's integers as resolve_hit forms it: the distance to the hit's plane,
+// in whole units, over the direction's component.  False: not settled (the
+// cell is then tested in whole numbers).  oz() gives the origin's height.
+template <class OzFn>
+__device__ __forceinline__ bool skim_sure_hit(const skim_ray& f, const skim_t& s, uint32_t v,
+                                              float ze, int32_t W, OzFn oz, uint32_t& word,
+                                              float& depth) {
+  const bool down = f.dz < 0.0f;
+  const float m2 = f.zhi - f.zlo, md = down ? m2 : 0.0f, mu = m2 - md;
+  const float zil = s.zin - md, zih = s.zin + mu, zel = ze - mu, zeh = ze + md;
+  const float F = (float)(v & 0xFF), B = (float)((v >> 8) & 0xFF), T = (float)((v >> 16) & 0xFF);
+  const bool two = (v & 0xFF00) != 0;
+  const bool in_floor = zih <= F;
+  const bool in_slab = two & (zil >= B) & (zih <= T);
+  const bool below = zih < B, above = two & (zil > T);
+  const bool out = (zil > F) & (!two | below | above);
+  const bool plane = out & (down ? zeh <= (above ? T : F) : (two & below & (zel >= B)));
+  const bool entry = in_floor | in_slab;
+  // the face entered through: the later of the near crossings
+  const bool fx = f.dx >= 0.0f, fy = f.dy >= 0.0f;
+  const int32_t X = s.x + (fx ? 0 : 1), Y = s.y + (fy ? 0 : 1);
+  const float tx = ((float)(X - f.cx) - f.fx) * f.rx;
+  const float ty = ((float)(Y - f.cy) - f.fy) * f.ry;
+  const bool ax = tx > ty;
+  const bool axis_sure = fabsf(tx - ty) > fmaxf(tx, ty) * 0x1p-20f & fmaxf(tx, ty) > 0.0f;
+  if (!(plane | (entry & axis_sure))) return false;
+  const int32_t h = down ? (int32_t)(above ? (v >> 16) & 0xFF : v & 0xFF)
+                         : (int32_t)((v >> 8) & 0xFF);
+  // origin (cells and fraction, or the height) and plane of the hit's axis
+  const int32_t oc = ax ? f.cx : f.cy;
+  const float of = ax ? f.fx : f.fy;
+  const int32_t O = entry ? (int32_t)((uint32_t)oc << 16) + (int32_t)(of * 65536.0f) : oz();
+  const int32_t P = entry ? (ax ? X : Y) : h;
+  const float D = entry ? (ax ? f.dx : f.dy) : f.dz;
+  const int32_t face = entry ? (ax ? (fx ? kWmx : kWpx) : (fy ? kWmy : kWpy))
+                             : (down ? kTop : kUnder);
+  const bool slab = entry ? !in_floor : (above | !down);
+  word = (uint32_t)(s.y * W + s.x) | ((uint32_t)face << 27) | (slab ? 1u << 30 : 0u);
+  // (the length is not to be computed ahead of the walk and held through it)
+  float Dx = f.dx;
+  asm volatile("" : "+v"(Dx));
+  depth = hit_depth(fma((double)P, 65536.0, -(double)O), fabs((double)D), Dx, f.dy, f.dz);
+  return true;
+}
+
+// The whole walk: its state (kHitCell with the record in word and depth,
+// kMissed, or kWalking when the budget ran out).  With kBoost a wave raises
+// its issue priority after boost, 2 boost and 4 boost steps (an instance of
+// its own: the stops cost the walk 1.4 %).
+template <bool kBoost, class RayFn, class OzFn>
+__device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
+                                             const skim_ray& f, skim_t& s, int32_t max_level,
+                                             int32_t budget, int32_t boost, int32_t& reads,
+                                             bool count, RayFn ray, OzFn oz, uint32_t& word,
+                                             float& depth) {
+  int32_t it = 0;
+  uint32_t col = 0;
+  float ze = 0.0f;
+  const bool down = f.dz < 0.0f;
+  int32_t stop = kBoost ? min(boost, budget) : budget;
+  for (;;) {
+    int32_t st;
+    if (down)
+      st = skim_steps<1>(m, lv, f, s, max_level, stop, it, col, ze, reads, count, ray);
+    else
+      st = skim_steps<2>(m, lv, f, s, max_level, stop, it, col, ze, reads, count, ray);
+    if (kBoost && stop < budget && st == kWalking) {
+      if (stop == boost) __builtin_amdgcn_s_setprio(1);
+      else if (stop == 2 * boost) __builtin_amdgcn_s_setprio(2);
+      else __builtin_amdgcn_s_setprio(3);
+      stop = stop < 4 * boost ? min(2 * stop, budget) : budget;
+      continue;
+    }
+    if (st != kHitCell) return st;
+    if (__builtin_expect(skim_sure_hit(f, s, col, ze, m.W, oz, word, depth), 1)) return kHitCell;
+    const skim_cell c = skim_exact_cell(ray(), s.x, s.y, col, m.W);
+    if (c.hit) {
+      word = c.word;
+      depth = __uint_as_float(c.depth);
+      return kHitCell;
+    }
+    // within the margin of solid, but not in it: on to the next cell
+    const skim_next n = skim_exact_step(ray(), s.x, s.y, 0);
+    const float t = n.ex ? ((float)(s.x + (f.dx >= 0.0f ? 1 : 0) - f.cx) - f.fx) * f.rx
+                         : ((float)(s.y + (f.dy >= 0.0f ? 1 : 0) - f.cy) - f.fy) * f.ry;
+    s.x = n.x;
+    s.y = n.y;
+    s.zin = fmaf(t, f.dz, down ? f.zhi : f.zlo);
+    ++it;
+  }
+}
+
+}  // namespace

@@ -308,6 +308,31 @@ __device__ __forceinline__ void walk_at_origin(const ray_t& r, int32_t L0, walk_
   s.reads = 0;
 }
 
+// Depth of a hit at time tn / td (units over a direction component, both
+// whole; td > 0) of a ray of direction (dx, dy, dz), whole numbers: |tn / td|
+// times the direction's length, in double precision, rounded once.  The
+// quotient and the root come from the hardware's estimates and Newton
+// steps, within about one unit in the double's last place; the general
+// division and square root, which also handle ranges that whole numbers
+// below 2^48 do not reach, take twenty more instructions (1.4 % of the
+// headline frame).
+__device__ __forceinline__ float hit_depth(double tn, double td, double dx, double dy,
+                                           double dz) {
+  const double l2 = fma(dx, dx, fma(dy, dy, dz * dz));   // exact: below 2^48
+  const double y = __builtin_amdgcn_rsq(l2);
+  double g = l2 * y, h = 0.5 * y;
+  const double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  const double len = fma(fma(-g, g, l2), h, g);
+  double r = __builtin_amdgcn_rcp(td);
+  r = fma(fma(-r, td, 1.0), r, r);
+  r = fma(fma(-r, td, 1.0), r, r);
+  double q = tn * r;
+  q = fma(fma(-q, td, tn), r, q);
+  return (float)(fabs(q) * len * (1.0 / 65536.0));
+}
+
 __device__ __forceinline__ void set_hit(const ray_t& r, int32_t W, int32_t x,
                                         int32_t y, int32_t face,
                                         int32_t layer, int64_t tn,
@@ -315,10 +340,7 @@ __device__ __forceinline__ void set_hit(const ray_t& r, int32_t W, int32_t x,
                                         float& depth) {
   word = (uint32_t)(y * W + x) | ((uint32_t)face << 27) |
          ((uint32_t)layer << 30);
-  double len = sqrt((double)r.Dx * r.Dx + (double)r.Dy * r.Dy +
-                    (double)r.Dz * r.Dz);
-  depth = tn == 0 ? 0.0f
-                  : (float)(((double)tn / (double)td) * len / 65536.0);
+  depth = hit_depth((double)tn, (double)td, (double)r.Dx, (double)r.Dy, (double)r.Dz);
 }
 
 // First hit inside cell (x, y) (packed column v), entered with height zin
