@@ -434,9 +434,14 @@ tc_status tc_load_columns(tc_context* ctx, int32_t W, int32_t H,
     }
     d.base = map;
     const uint8_t* src[3] = {floor_top, slab_bottom, slab_top};
-    for (int k = 0; k < 3 && e == hipSuccess; ++k)
-      e = hipMemcpy2DAsync(planes + (size_t)k * W * H, W, src[k], row_stride, W,
-                           H, hipMemcpyHostToDevice, s);
+    // (rows without gaps go as one copy: the 2D copy of pageable memory runs
+    // row by row, 149 ms for a plane of 2048 x 16384 against 1.3 ms)
+    for (int k = 0; k < 3 && e == hipSuccess; ++k) {
+      uint8_t* dst = planes + (size_t)k * W * H;
+      e = row_stride == (size_t)W
+              ? hipMemcpyAsync(dst, src[k], (size_t)W * H, hipMemcpyHostToDevice, s)
+              : hipMemcpy2DAsync(dst, W, src[k], row_stride, W, H, hipMemcpyHostToDevice, s);
+    }
     if (e == hipSuccess) e = tci_launch_repack(planes, W, H, map, d.lv[0], s);
     for (int32_t L = 1; L <= d.top && e == hipSuccess; ++L)
       e = tci_launch_build_level(d, map, L, s);
