@@ -434,13 +434,21 @@ tc_status tc_load_columns(tc_context* ctx, int32_t W, int32_t H,
     }
     d.base = map;
     const uint8_t* src[3] = {floor_top, slab_bottom, slab_top};
-    // (rows without gaps go as one copy: the 2D copy of pageable memory runs
-    // row by row, 149 ms for a plane of 2048 x 16384 against 1.3 ms)
+    // each plane as one copy (a 2D copy of pageable memory runs row by row,
+    // 149 ms for a plane of 2048 x 16384 against 1.3 ms); rows with gaps are
+    // packed first
+    std::vector<uint8_t> packed;
     for (int k = 0; k < 3 && e == hipSuccess; ++k) {
-      uint8_t* dst = planes + (size_t)k * W * H;
-      e = row_stride == (size_t)W
-              ? hipMemcpyAsync(dst, src[k], (size_t)W * H, hipMemcpyHostToDevice, s)
-              : hipMemcpy2DAsync(dst, W, src[k], row_stride, W, H, hipMemcpyHostToDevice, s);
+      const uint8_t* rows = src[k];
+      if (row_stride != (size_t)W) {
+        packed.resize((size_t)W * H);
+        for (int32_t y = 0; y < H; ++y)
+          std::memcpy(packed.data() + (size_t)y * W, rows + (size_t)y * row_stride, W);
+        rows = packed.data();
+      }
+      e = hipMemcpyAsync(planes + (size_t)k * W * H, rows, (size_t)W * H, hipMemcpyHostToDevice, s);
+      // (the packed rows are overwritten by the next plane's)
+      if (e == hipSuccess && !packed.empty()) e = hipStreamSynchronize(s);
     }
     if (e == hipSuccess) e = tci_launch_repack(planes, W, H, map, d.lv[0], s);
     for (int32_t L = 1; L <= d.top && e == hipSuccess; ++L)
@@ -611,6 +619,16 @@ tc_status tc_shade_views(tc_context* ctx, const tc_view* views, int32_t n,
     hipError_t e = hipMemcpyAsync(slot->dev, slot->host, total, hipMemcpyHostToDevice, s);
     tci_shade sh;
     for (int c = 0; c < 3; ++c) sh.light[c] = p.light[c];
+    {
+      // one IEEE single operation at a time, as the shading's definition has it
+#pragma clang fp contract(off)
+      const float Lx = (float)p.light[0], Ly = (float)p.light[1], Lz = (float)p.light[2];
+      const float xx = Lx * Lx, yy = Ly * Ly, zz = Lz * Lz;
+      const float ll = sqrtf((xx + yy) + zz);
+      sh.unit[0] = Lx / ll;
+      sh.unit[1] = Ly / ll;
+      sh.unit[2] = Lz / ll;
+    }
     sh.ambient = p.ambient;
     sh.cave_ambient = p.cave_ambient;
     sh.fog_far = p.fog_far;

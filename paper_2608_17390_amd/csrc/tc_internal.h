@@ -63,6 +63,7 @@ struct tci_inline {
 // Shading parameters (the device copy of tc_shade_params).
 struct tci_shade {
   int32_t light[3];            // integer direction toward the light
+  float unit[3];               // the same over its length, in single precision
   float ambient, cave_ambient, fog_far;
   uint32_t sky_rgba, fog_rgba;
   const uint32_t* palette;     // 512 RGBA entries in device memory

@@ -304,6 +304,16 @@ __device__ __forceinline__ bool skim_sure_hit(const skim_ray& f, const skim_t& s
   return true;
 }
 
+// The step out of the current cell (level 0) in whole numbers.
+__device__ __forceinline__ void skim_step_whole(const skim_ray& f, skim_t& s, const skim_int& q) {
+  const skim_next n = skim_exact_step(q, s.x, s.y, 0);
+  const float t = n.ex ? ((float)(s.x + (f.dx >= 0.0f ? 1 : 0) - f.cx) - f.fx) * f.rx
+                       : ((float)(s.y + (f.dy >= 0.0f ? 1 : 0) - f.cy) - f.fy) * f.ry;
+  s.x = n.x;
+  s.y = n.y;
+  s.zin = fmaf(t, f.dz, f.dz < 0.0f ? f.zhi : f.zlo);
+}
+
 // The whole walk: its state (kHitCell with the record in word and depth,
 // kMissed, or kWalking when the budget ran out).  With kBoost a wave raises
 // its issue priority after boost, 2 boost and 4 boost steps (an instance of
@@ -341,12 +351,85 @@ __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
       return kHitCell;
     }
     // within the margin of solid, but not in it: on to the next cell
-    const skim_next n = skim_exact_step(ray(), s.x, s.y, 0);
-    const float t = n.ex ? ((float)(s.x + (f.dx >= 0.0f ? 1 : 0) - f.cx) - f.fx) * f.rx
-                         : ((float)(s.y + (f.dy >= 0.0f ? 1 : 0) - f.cy) - f.fy) * f.ry;
-    s.x = n.x;
-    s.y = n.y;
-    s.zin = fmaf(t, f.dz, down ? f.zhi : f.zlo);
+    skim_step_whole(f, s, ray());
+    ++it;
+  }
+}
+
+// Does the ray (its integers in q) meet any solid?  Its origin usually lies
+// a unit off a surface, far inside the margin, so in the origin's cell the
+// entry is compared in whole numbers and the exit alone with the margin;
+// the walk proper begins in the next cell.  A walk that uses up its bound
+// (never expected) counts as a hit.
+template <int kDir, bool kCount>
+__device__ __forceinline__ bool skim_blocked(const tci_map& m, const lvl_t* lv, const skim_int& q,
+                                             int32_t max_level, int32_t& reads) {
+  constexpr bool desc = kDir == 1;
+  skim_ray f;
+  skim_t s;
+  skim_init(skim_whole(q), f);
+  const float m2 = f.zhi - f.zlo;
+  {
+    const lvl_t l = lv[0];
+    const int32_t x = f.cx, y = f.cy;
+    const bool fx = f.dx >= 0.0f, fy = f.dy >= 0.0f;
+    const bool inmap = ((uint32_t)x <= (uint32_t)l.w1) & ((uint32_t)y <= (uint32_t)l.h1);
+    const uint32_t ci = (uint32_t)clamp0(x, l.w1), cj = (uint32_t)clamp0(y, l.h1);
+    const uint32_t v = map_word(m.base, l.off + ((umul24(cj >> 3, (uint32_t)l.tiles_x) + (ci >> 3)) << 6) +
+                                            ((cj & 7) << 3) + (ci & 7));
+    if (kCount) reads += inmap ? 1 : 0;
+    const float tx = ((fx ? 1.0f : 0.0f) - f.fx) * f.rx, ty = ((fy ? 1.0f : 0.0f) - f.fy) * f.ry;
+    const bool ex = tx <= ty;
+    const float te = fminf(tx, ty);
+    const float zl = fmaf(te, f.dz, f.zlo), zh = fmaf(te, f.dz, f.zhi);
+    const float F = (float)(v & 0xFF), B = (float)((v >> 8) & 0xFF), T = (float)((v >> 16) & 0xFF);
+    const int32_t F16 = (int32_t)(v & 0xFF) << 16, B16 = (int32_t)(v & 0xFF00) << 8,
+                  T16 = (int32_t)(v & 0xFF0000);
+    const bool two = (v & 0xFF00) != 0;
+    const bool in = (q.Oz <= F16) | (two & (q.Oz >= B16) & (q.Oz <= T16));
+    bool maybe, sure;
+    if (desc) {
+      const bool over = two & (q.Oz > T16);
+      maybe = (zl <= F) | (over & (zl <= T));
+      sure = (zh <= F) | (over & (zh <= T));
+    } else {
+      const bool under = two & (q.Oz < B16);
+      maybe = under & (zh >= B);
+      sure = under & (zl >= B);
+    }
+    if (inmap & (in | sure)) return true;
+    if (__builtin_expect(inmap & maybe, 0))
+      if (skim_exact_cell(q, x, y, v, m.W).hit) return true;
+    const bool away = ((x < 0) & (f.dx <= 0.0f)) | ((x > l.w1) & fx) |
+                      ((y < 0) & (f.dy <= 0.0f)) | ((y > l.h1) & fy);
+    if (away) return false;
+    const float p = fmaf(te, ex ? f.dy : f.dx, ex ? f.fy : f.fx);
+    s.L = 0;
+    s.x = x;
+    s.y = y;
+    if (__builtin_expect(skim_sure(p), 1)) {
+      const int32_t o = (int32_t)floorf(p);
+      s.x += ex ? (fx ? 1 : -1) : o;
+      s.y += ex ? o : (fy ? 1 : -1);
+      s.zin = desc ? zh : zl;
+    } else {
+      skim_step_whole(f, s, q);
+    }
+  }
+  int32_t it = 0;
+  for (;;) {
+    uint32_t v = 0;
+    float ze = 0.0f;
+    const int32_t st = skim_steps<kDir>(m, lv, f, s, max_level, kIterCap + 1, it, v, ze, reads,
+                                        kCount, [&]() { return q; });
+    if (st != kHitCell) return st != kMissed;
+    // surely in solid, also with the heights moved by the margin the other
+    // way; or else tested in whole numbers
+    const float lo = (desc ? ze : s.zin) + m2, hi = (desc ? s.zin : ze) - m2;
+    const float F = (float)(v & 0xFF), B = (float)((v >> 8) & 0xFF), T = (float)((v >> 16) & 0xFF);
+    if (__builtin_expect((lo <= F) | (((v & 0xFF00) != 0) & (lo <= T) & (hi >= B)), 1)) return true;
+    if (skim_exact_cell(q, s.x, s.y, v, m.W).hit) return true;
+    skim_step_whole(f, s, q);
     ++it;
   }
 }
