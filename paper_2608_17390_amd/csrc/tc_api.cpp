@@ -165,32 +165,46 @@ tci_render_opts render_opts(const tc_context* c) {
 hipError_t enqueue_edits(const tci_map& d, uint32_t* map, const char* dev,
                          const EditPlan& p, hipStream_t s, const tci_voxels* vx,
                          uint32_t* vox, uint64_t* zero, int32_t nzero) {
-  hipError_t e = tci_launch_edits((const tci_edit*)(dev + p.off_edits), p.n,
-                                  (const int32_t*)(dev + p.off_olap), p.olap_all,
-                                  (const uint8_t*)(dev + p.off_patch), map, d.lv[0],
-                                  d.W, d.H, p.max_w, p.max_h, s);
+  // short lists: the cells and levels 1..6 in one launch, then the levels
+  // above from level 6; longer ones: the cells, then all levels
+  const bool tiles = tci_edit_tiles(p.n);
+  const tci_edit* ed = (const tci_edit*)(dev + p.off_edits);
+  const uint8_t* patch = (const uint8_t*)(dev + p.off_patch);
+  hipError_t e = tiles ? tci_launch_edit_tiles(d, ed, p.n, patch, map, p.max_w, p.max_h, s)
+                       : tci_launch_edits(ed, p.n, (const int32_t*)(dev + p.off_olap), p.olap_all,
+                                          patch, map, d.lv[0], d.W, d.H, p.max_w, p.max_h, s);
   const int32_t* rects = (const int32_t*)(dev + p.off_rects);
-  // upward in groups of kUpdateGroup levels, one launch each: the dirty
-  // nodes of levels s + 1 .. e and the window entries of levels s .. e - 1
-  // (the top group: s .. e) whose 2 x 2 node block meets an edited node,
-  // all computed from level s (each launch is a node of its own in a
-  // captured frame, and a few microseconds however little it does)
+  const int32_t nr = p.nrect[0];
   if (p.top == 0 && e == hipSuccess)
-    e = tci_launch_update_window(d, map, 0, rects, p.nrect[0], p.rmw[0] + 1, p.rmh[0] + 1, s,
-                                 zero, nzero);
-  for (int32_t s0 = 0; s0 < p.top && e == hipSuccess; s0 += kUpdateGroup) {
-    const int32_t e0 = std::min(s0 + kUpdateGroup, p.top);
-    const bool last = e0 == p.top;
+    e = tci_launch_update_window(d, map, 0, rects, nr, p.rmw[0] + 1, p.rmh[0] + 1, s, zero, nzero);
+  // upward in groups of kUpdateGroup levels, one launch each: the dirty
+  // nodes of levels s + 1 .. e and the window entries of levels w0 .. e - 1
+  // (the top group: w0 .. e) whose 2 x 2 node block meets an edited node,
+  // all computed from level s (each launch is a node of its own in a
+  // captured frame, and a few microseconds however little it does); once the
+  // levels above hold few nodes, one launch computes all of them
+  int32_t s0 = tiles ? std::min(p.top, 6) : 0, w0 = 0;
+  bool done = p.top == 0;
+  while (!done && e == hipSuccess) {
+    const bool top = tci_update_top(d, s0);
+    const int32_t e0 = top ? s0 : std::min(s0 + kUpdateGroup, p.top);
+    done = top || e0 == p.top;
     // lanes of the largest job: a node of level L takes 2^(L - s0) lanes,
-    // a window entry 2^(L - s0 + 1)
+    // a window entry 2^(L - s0 + 1), or 2 up to level s0
     int64_t lanes = 1;
-    for (int32_t L = s0; L <= e0; ++L) {
+    for (int32_t L = w0; L <= e0; ++L) {
       if (L > s0) lanes = std::max<int64_t>(lanes, ((int64_t)p.rmw[L] * p.rmh[L]) << (L - s0));
-      if (L < e0 || last)
-        lanes = std::max<int64_t>(lanes, ((int64_t)(p.rmw[L] + 1) * (p.rmh[L] + 1)) << (L - s0 + 1));
+      if (L < e0 || done)
+        lanes = std::max<int64_t>(lanes, ((int64_t)(p.rmw[L] + 1) * (p.rmh[L] + 1))
+                                             << (std::max(L - s0, 0) + 1));
     }
-    e = tci_launch_update_group(d, map, s0, e0, last, rects, p.n, p.nrect[0], lanes, s,
-                                last ? zero : nullptr, last ? nzero : 0);
+    if (top) {
+      e = tci_launch_update_top(d, map, s0, w0, rects, p.n, nr, lanes, s, zero, nzero);
+      break;
+    }
+    e = tci_launch_update_group(d, map, s0, e0, w0, done, rects, p.n, nr, lanes, s,
+                                done ? zero : nullptr, done ? nzero : 0);
+    s0 = w0 = e0;
   }
   // and the voxel tiles over the edited cells, level by level upward
   if (vx && vox) {

@@ -80,20 +80,36 @@ hipError_t tci_launch_edits(const tci_edit* edits, int32_t n, const int32_t* ola
                             bool olap_all, const uint8_t* patch, uint32_t* base,
                             tci_level l0, int32_t W, int32_t H,
                             int32_t max_w, int32_t max_h, hipStream_t s);
+// The same for short lists (tci_edit_tiles), which also recomputes the nodes
+// and masks of levels 1..6 (up to the top) over the rectangles; max_w x
+// max_h bounds any clipped rectangle.
+bool tci_edit_tiles(int32_t n);
+hipError_t tci_launch_edit_tiles(const tci_map& m, const tci_edit* edits, int32_t n,
+                                 const uint8_t* patch, uint32_t* base, int32_t max_w,
+                                 int32_t max_h, hipStream_t s);
 // One launch per group of levels s + 1 .. e after edits: recompute the
 // nodes (and occupancy masks) of those levels over their rectangles and the
-// window entries of levels s .. e - 1, with wtop s .. e, over theirs
-// (entries x0 - 1 .. x1, y0 - 1 .. y1), all from level s, which must be up
-// to date (e - s <= 3).  The launch also clears zero[0 .. nzero) (nzero <=
-// 256), or a launch of its own does if there is nothing to update.  rects holds
-// nr rectangles per level (x0, y0, x1, y1 inclusive, in that level's node
-// coordinates), level L's at rects + 4 * (L * stride + r); max_lanes bounds
-// the lanes of any one rectangle job (2^(L - s) per node of level L,
-// 2^(L - s + 1) per window entry).
+// window entries of levels w0 .. e - 1 (w0 <= s), with wtop w0 .. e, over
+// theirs (entries x0 - 1 .. x1, y0 - 1 .. y1), all from level s, which must
+// be up to date, as must w0 .. s - 1 (e - s <= 3).  The launch also clears
+// zero[0 .. nzero) (nzero <= 256), or a launch of its own does if there is
+// nothing to update.  rects holds nr rectangles per level (x0, y0, x1, y1
+// inclusive, in that level's node coordinates), level L's at
+// rects + 4 * (L * stride + r); max_lanes bounds the lanes of any one
+// rectangle job (2^(L - s) per node of level L, 2^(L - s + 1) per window
+// entry, 2 below level s).
 hipError_t tci_launch_update_group(const tci_map& m, uint32_t* base, int32_t s, int32_t e,
-                                   bool wtop, const int32_t* rects, int32_t stride, int32_t nr,
-                                   int64_t max_lanes, hipStream_t st, uint64_t* zero = nullptr,
-                                   int32_t nzero = 0);
+                                   int32_t w0, bool wtop, const int32_t* rects, int32_t stride,
+                                   int32_t nr, int64_t max_lanes, hipStream_t st,
+                                   uint64_t* zero = nullptr, int32_t nzero = 0);
+// All levels above s (nodes, masks and windows) and the window entries of
+// levels w0 .. s over their rectangles, in one launch; possible where
+// tci_update_top says so.  Other arguments as above.
+bool tci_update_top(const tci_map& m, int32_t s);
+hipError_t tci_launch_update_top(const tci_map& m, uint32_t* base, int32_t s, int32_t w0,
+                                 const int32_t* rects, int32_t stride, int32_t nr,
+                                 int64_t max_lanes, hipStream_t st, uint64_t* zero,
+                                 int32_t nzero);
 
 // Window level L from level L (all entries), and its entries whose node
 // block meets one of the level-L rectangles (x0, y0, x1, y1 inclusive):

@@ -207,6 +207,190 @@ __global__ void edits_kernel(const tci_edit* __restrict__ edits, int32_t n,
   }
 }
 
+// Edits and the six pyramid levels over them in one launch, for lists of at
+// most kTileEdits edits.  A block takes a block of 64 x 64 cells that an
+// edit's rectangle touches, a wave 16 x 16 of them, a lane 2 x 2: it applies
+// every edit that covers its cells, in list order, and has the node and mask
+// of level 1 at hand; those of levels 2..4 fold together by cross-lane
+// exchanges, and the first wave folds the block's 16 level-4 nodes into those
+// of levels 5 and 6.  A block of cells belongs to the first edit that touches
+// it (64 edits are compared at a time, one per lane), so no two blocks write
+// the same word; cells and nodes no edit touches come out as they were.
+// grid.x = edit; grid.y blocks stride over its blocks of cells.  Every launch
+// of an edit's chain is bound by latency: a few microseconds however little
+// it does, of which one round of loads and the first fetch of its own code
+// are most.  So it pays to have fewer of them, each with one round of loads
+// and little code: the chain of a 96-cell crater on a 2048 x 16384 map was six
+// launches (one for the cells, five for the levels) of 25 us together and is
+// two of 17 (7 this one).  Longer lists than kTileEdits compare too many
+// edits per block of cells and keep the launch per cells and per level group.
+constexpr int32_t kTileEdits = 512;
+constexpr int32_t kTileThreads = 1024;
+
+// The levels' records in LDS: a kernel that goes through the levels in turn
+// then waits for the kernel's arguments once.
+struct levels_t {
+  tci_level lv[TCI_MAX_LEVELS], mk[TCI_MAX_LEVELS], wl[TCI_MAX_LEVELS];
+};
+__device__ inline void load_levels_lds(const tci_map& m, levels_t& t) {
+  const int32_t k = threadIdx.x >> 6, L = threadIdx.x & 63;
+  if (L < TCI_MAX_LEVELS) {
+    if (k == 0) t.lv[L] = m.lv[L];
+    else if (k == 1) t.mk[L] = m.mk[L];
+    else if (k == 2) t.wl[L] = m.wl[L];
+  }
+  __syncthreads();
+}
+
+// An edit's rectangle clipped to the map: cells x0..x1, y0..y1, empty if
+// x0 > x1 or y0 > y1.
+struct clip_t {
+  int32_t x0, y0, x1, y1;
+};
+__device__ inline clip_t clip(const tci_edit& e, int32_t W, int32_t H) {
+  return clip_t{max(e.x0, 0), max(e.y0, 0), min(e.x0 + e.w, W) - 1, min(e.y0 + e.h, H) - 1};
+}
+// Does it touch block (bx, by) of 2^sh x 2^sh cells?
+__device__ inline bool touches(const clip_t& r, int32_t bx, int32_t by, int32_t sh) {
+  return (r.x0 <= r.x1) & (r.y0 <= r.y1) & ((r.x0 >> sh) <= bx) & (bx <= (r.x1 >> sh)) &
+         ((r.y0 >> sh) <= by) & (by <= (r.y1 >> sh));
+}
+
+// Lane ^ o's word, without the LDS round trip of a general exchange where
+// the hardware moves lanes itself (o = 1, 2: within four lanes; 8: half a
+// turn of 16).
+template <int o>
+__device__ inline uint32_t from_lane_xor(uint32_t v) {
+  if constexpr (o == 1) return __builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);
+  else if constexpr (o == 2) return __builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);
+  else if constexpr (o == 8) return __builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);
+  else return (uint32_t)__shfl_xor((int)v, o);
+}
+
+template <int o>
+__device__ inline void fold_step(uint32_t& v, uint64_t& mk) {
+  v = node_merge(v, from_lane_xor<o>(v));
+  const uint32_t lo = from_lane_xor<o>((uint32_t)mk);
+  const uint32_t hi = from_lane_xor<o>((uint32_t)(mk >> 32));
+  mk |= (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
+// The nodes and masks of levels L0 + 1 .. L0 + n (n <= 3) over 8 x 8
+// level-L0 nodes (v, mk) held one per lane: that of lane k at (x, y), its
+// place in the block (k & 7, k >> 3), in: inside the level.  The lane of each
+// node's first level-L0 node stores it and hands it to put(level, x, y,
+// node, mask); v and mk end as the level L0 + 3 node's.
+template <class Put>
+__device__ inline void fold_levels(const levels_t& t, int32_t top, uint32_t* base, int32_t L0,
+                                   int32_t n, int32_t x, int32_t y, bool in, int32_t lane,
+                                   uint32_t& v, uint64_t& mk, Put put) {
+  auto store = [&](int32_t k) {
+    if (L0 + k > top || k > n || !in || (((lane & 7) | (lane >> 3)) & ((1 << k) - 1)) != 0) return;
+    const int32_t i = x >> k, j = y >> k;
+    base[tci_tile_index(t.lv[L0 + k], i, j)] = v;
+    *reinterpret_cast<uint2*>(base + tci_mask_index(t.mk[L0 + k], i, j)) =
+        make_uint2((uint32_t)mk, (uint32_t)(mk >> 32));
+    put(L0 + k, i, j, v, mk);
+  };
+  fold_step<1>(v, mk);
+  fold_step<8>(v, mk);
+  store(1);
+  fold_step<2>(v, mk);
+  fold_step<16>(v, mk);
+  store(2);
+  fold_step<4>(v, mk);
+  fold_step<32>(v, mk);
+  store(3);
+}
+
+__global__ __launch_bounds__(kTileThreads) void edit_tiles_kernel(
+    tci_map m, const tci_edit* __restrict__ edits, int32_t n, const uint8_t* __restrict__ patch,
+    uint32_t* __restrict__ base) {
+  __shared__ levels_t tab;
+  __shared__ uint32_t node4[16], lo4[16], hi4[16];
+  const int32_t ei = blockIdx.x, lane = threadIdx.x & 63;
+  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const clip_t r = clip(edits[ei], m.W, m.H);
+  if (r.x0 > r.x1 || r.y0 > r.y1) return;
+  // the first 64 edits' rectangles, one per lane
+  const clip_t mine = clip(edits[min(lane, n - 1)], m.W, m.H);
+  load_levels_lds(m, tab);
+  const int32_t bx0 = r.x0 >> 6, by0 = r.y0 >> 6;
+  const int32_t nbx = (r.x1 >> 6) - bx0 + 1, nb = nbx * ((r.y1 >> 6) - by0 + 1);
+  // which of edits c .. c + 63 touch the block (all lanes take part)
+  auto who = [&](int32_t c, int32_t bx, int32_t by) {
+    const clip_t q = c == 0 ? mine : clip(edits[min(c + lane, n - 1)], m.W, m.H);
+    return (uint64_t)__ballot(c + lane < n && touches(q, bx, by, 6));
+  };
+  // (every wave of the block runs the same rounds: the barriers are reached
+  // by all of them)
+  for (int32_t b = blockIdx.y; b < nb; b += gridDim.y) {
+    const int32_t bx = bx0 + b % nbx, by = by0 + b / nbx;
+    // the lane's four cells: two pairs in memory (tiles are whole, so the
+    // cells of a lane whose first is in the map can be read)
+    const int32_t x1 = bx * 32 + (wave & 3) * 8 + (lane & 7), y1 = by * 32 + (wave >> 2) * 8 + (lane >> 3);
+    const int32_t x = 2 * x1, y = 2 * y1;
+    const bool in = x < m.W && y < m.H;
+    uint32_t* c0 = base + (in ? tci_tile_index(tab.lv[0], x, y) : 0u);
+    uint2 p[2] = {make_uint2(0u, 0u), make_uint2(0u, 0u)};
+    if (in) {
+      p[0] = *reinterpret_cast<const uint2*>(c0);
+      p[1] = *reinterpret_cast<const uint2*>(c0 + 8);
+    }
+    bool owned = true;
+    for (int32_t c = 0; c <= ei && owned; c += 64)
+      owned = (who(c, bx, by) & (ei - c < 64 ? (1ull << (ei - c)) - 1 : ~0ull)) == 0;
+    if (!owned) continue;
+    for (int32_t c = ei & ~63; c < n; c += 64) {
+      uint64_t mask = who(c, bx, by);
+      while (mask) {
+        const int32_t k = c + __ffsll((unsigned long long)mask) - 1;
+        mask &= mask - 1;
+        const tci_edit& e = edits[k];
+#pragma unroll
+        for (int32_t d = 0; d < 4; ++d) {
+          const int32_t cx = x + (d & 1), cy = y + (d >> 1);
+          uint32_t& col = d & 1 ? p[d >> 1].y : p[d >> 1].x;
+          if (cx < m.W && cy < m.H && covers(e, cx, cy)) col = apply_one(e, patch, col, cx, cy);
+        }
+      }
+    }
+    if (in) {
+      *reinterpret_cast<uint2*>(c0) = p[0];
+      *reinterpret_cast<uint2*>(c0 + 8) = p[1];
+    }
+    // the level-1 node; a cell beside the map counts as empty (fmax 0, smin
+    // 255, smax 0), as the zero word there does
+    uint32_t v = node_merge(node_merge(cell_to_node(p[0].x), cell_to_node(p[0].y)),
+                            node_merge(cell_to_node(p[1].x), cell_to_node(p[1].y)));
+    uint64_t mk = cell_mask(p[0].x) | cell_mask(p[0].y) | cell_mask(p[1].x) | cell_mask(p[1].y);
+    if (in && m.top > 0) {
+      base[tci_tile_index(tab.lv[1], x1, y1)] = v;
+      *reinterpret_cast<uint2*>(base + tci_mask_index(tab.mk[1], x1, y1)) =
+          make_uint2((uint32_t)mk, (uint32_t)(mk >> 32));
+    }
+    auto none = [](int32_t, int32_t, int32_t, uint32_t, uint64_t) {};
+    fold_levels(tab, m.top, base, 1, 3, x1, y1, in, lane, v, mk, none);
+    if (lane == 0) {
+      node4[wave] = v;
+      lo4[wave] = (uint32_t)mk;
+      hi4[wave] = (uint32_t)(mk >> 32);
+    }
+    __syncthreads();
+    if (wave == 0 && m.top > 4) {
+      // the 4 x 4 level-4 nodes in the first corner of 8 x 8 lanes
+      const bool here = (lane & 7) < 4 && lane < 32;
+      const int32_t q = (lane & 3) + ((lane >> 3) & 3) * 4;
+      const int32_t x4 = bx * 4 + (lane & 7), y4 = by * 4 + (lane >> 3);
+      uint32_t v4 = here ? node4[q] : 255u << 8;
+      uint64_t k4 = here ? (uint64_t)lo4[q] | ((uint64_t)hi4[q] << 32) : 0;
+      fold_levels(tab, m.top, base, 4, 2, x4, y4, here && x4 * 16 < m.W && y4 * 16 < m.H, lane, v4,
+                  k4, none);
+    }
+    __syncthreads();
+  }
+}
+
 // Window entry (i, j) of level L: the combine of level-L nodes (i..i+1,
 // j..j+1) that exist (level 0: the cells, as nodes).
 __device__ inline uint32_t window_entry(const tci_map& m, const uint32_t* base, int32_t L,
@@ -341,10 +525,11 @@ __device__ inline void group_job(const tci_map& m, uint32_t* base, int32_t s, in
 }
 
 // One launch per group of levels after edits, reading only level s, which
-// the launch before finished (level 0, the cells, for the first group):
+// the launch before finished (level 0, the cells, for the first group), and
+// for window levels w0 .. s - 1 those levels themselves (finished as well):
 // blocks [0, (e - s) nr) recompute the dirty nodes and masks of levels
 // s + 1 .. e; the blocks after them the dirty window entries of levels
-// s .. e - 1, and with wtop of level e too (the top group).  Job j of either
+// w0 .. e - 1, and with wtop of level e too (the top group).  Job j of either
 // kind is level (first level) + j / nr, rectangle j % nr; the rectangles of
 // level L (x0, y0, x1, y1 inclusive, in level-L node coordinates) are at
 // rects + 4 (L stride + r).  Every output depends on level s alone, so no
@@ -354,13 +539,14 @@ __device__ inline void group_job(const tci_map& m, uint32_t* base, int32_t s, in
 // first block also clears zero[0 .. nzero) (a captured frame's render
 // counters, in the top group).
 __global__ void update_group_kernel(tci_map m, uint32_t* __restrict__ base, int32_t s,
-                                    int32_t e, int32_t wtop, const int32_t* __restrict__ rects,
-                                    int32_t stride, int32_t nr, uint64_t* zero, int32_t nzero) {
+                                    int32_t e, int32_t w0, int32_t wtop,
+                                    const int32_t* __restrict__ rects, int32_t stride,
+                                    int32_t nr, uint64_t* zero, int32_t nzero) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && (int32_t)threadIdx.x < nzero) zero[threadIdx.x] = 0;
   const int32_t nl = (e - s) * nr;
   const bool node_job = (int32_t)blockIdx.x < nl;
   const int32_t job = node_job ? (int32_t)blockIdx.x : (int32_t)blockIdx.x - nl;
-  const int32_t L = (node_job ? s + 1 : s) + job / nr;
+  const int32_t L = (node_job ? s + 1 : w0) + job / nr;
   const int32_t* r = rects + 4 * ((size_t)L * stride + job % nr);
   const int32_t k = L - s;
   int32_t x0 = r[0], y0 = r[1], x1 = r[2], y1 = r[3];
@@ -378,10 +564,116 @@ __global__ void update_group_kernel(tci_map m, uint32_t* __restrict__ base, int3
   x1 = min(x1, w.w - 1);
   y1 = min(y1, w.h - 1);
   if (x0 > x1 || y0 > y1) return;
-  if (k == 0) group_job<2, false>(m, base, s, L, x0, y0, x1, y1);
+  if (k <= 0) group_job<2, false>(m, base, L, L, x0, y0, x1, y1);
   else if (k == 1) group_job<4, false>(m, base, s, L, x0, y0, x1, y1);
   else if (k == 2) group_job<8, false>(m, base, s, L, x0, y0, x1, y1);
   else group_job<16, false>(m, base, s, L, x0, y0, x1, y1);
+}
+
+// The last launch after edits: all of the levels above s, where they hold
+// few nodes (at most kTopNodes together), whatever the edits touched.  Block
+// 0 computes them: a wave takes 8 x 8 nodes of level s + 1 from level s,
+// which the launch before finished, and folds them into three levels more;
+// the top of those is folded again from LDS, three levels to a barrier, up to
+// the last; then the window entries of all of them come from LDS.  10 us on
+// a 2048 x 16384 map (a barrier per level, with its stores between, took 20:
+// the waits for stores and for loads behind branches were most).  The other blocks compute
+// the dirty window entries of levels w0 .. s (job j of them level w0 + j / nr,
+// rectangle j % nr, as in update_group_kernel), from those levels.  The first
+// block also clears zero[0 .. nzero).
+constexpr int32_t kTopNodes = 5461;      // 4096 + 1024 + ... + 1
+constexpr int32_t kTopThreads = 1024;
+
+__global__ __launch_bounds__(kTopThreads) void update_top_kernel(tci_map m,
+                                                                 uint32_t* __restrict__ base,
+                                                                 int32_t s, int32_t w0,
+                                                                 const int32_t* __restrict__ rects,
+                                                                 int32_t stride, int32_t nr,
+                                                                 uint64_t* zero, int32_t nzero) {
+  __shared__ uint32_t node[kTopNodes];
+  __shared__ uint32_t mlo[kTopNodes], mhi[kTopNodes];
+  __shared__ int32_t first[TCI_MAX_LEVELS];    // each level's first node in them
+  __shared__ levels_t tab;
+  if (blockIdx.x > 0) {
+    const int32_t job = (int32_t)blockIdx.x - 1, L = w0 + job / nr;
+    const int32_t* r = rects + 4 * ((size_t)L * stride + job % nr);
+    const tci_level& w = m.wl[L];
+    const int32_t x0 = max(r[0] - 1, 0), y0 = max(r[1] - 1, 0);
+    const int32_t x1 = min(r[2], w.w - 1), y1 = min(r[3], w.h - 1);
+    if (x0 <= x1 && y0 <= y1) group_job<2, false>(m, base, L, L, x0, y0, x1, y1);
+    return;
+  }
+  if (blockIdx.y > 0) return;
+  if ((int32_t)threadIdx.x < nzero) zero[threadIdx.x] = 0;
+  const int32_t lane = threadIdx.x & 63;
+  const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  load_levels_lds(m, tab);
+  if (threadIdx.x < TCI_MAX_LEVELS) {
+    int32_t at = 0;
+    for (int32_t L = s + 1; L < (int32_t)threadIdx.x; ++L) at += tab.lv[L].w * tab.lv[L].h;
+    first[threadIdx.x] = at;
+  }
+  __syncthreads();
+  auto put = [&](int32_t L, int32_t i, int32_t j, uint32_t v, uint64_t mk) {
+    const int32_t q = first[L] + j * tab.lv[L].w + i;
+    node[q] = v;
+    mlo[q] = (uint32_t)mk;
+    mhi[q] = (uint32_t)(mk >> 32);
+  };
+  for (int32_t L = s + 1;; L += 3) {
+    // 8 x 8 blocks of level L: from level s, or from LDS
+    const tci_level l = tab.lv[L];
+    const int32_t tw = (l.w + 7) >> 3, nt = tw * ((l.h + 7) >> 3);
+    for (int32_t t = wave; t < nt; t += kTopThreads / 64) {
+      const int32_t x = (t % tw) * 8 + (lane & 7), y = (t / tw) * 8 + (lane >> 3);
+      const bool in = x < l.w && y < l.h;
+      uint32_t v = 255u << 8;   // (empty: fmax 0, smin 255, smax 0)
+      uint64_t mk = 0;
+      if (L == s + 1) {
+        // a child beside its level stands for its neighbour inside it,
+        // which changes no combine: no branch stands between the loads
+        const tci_level c = tab.lv[s], cm = tab.mk[s];
+        uint32_t cv[4];
+        uint2 ck[4];
+#pragma unroll
+        for (int32_t d = 0; d < 4; ++d) {
+          const int32_t i = min(2 * x + (d & 1), c.w - 1), j = min(2 * y + (d >> 1), c.h - 1);
+          cv[d] = base[tci_tile_index(c, i, j)];
+          ck[d] = *reinterpret_cast<const uint2*>(base + tci_mask_index(cm, i, j));
+        }
+        if (in) {
+          v = node_merge(node_merge(cv[0], cv[1]), node_merge(cv[2], cv[3]));
+          mk = (uint64_t)(ck[0].x | ck[1].x | ck[2].x | ck[3].x) |
+               ((uint64_t)(ck[0].y | ck[1].y | ck[2].y | ck[3].y) << 32);
+          base[tci_tile_index(l, x, y)] = v;
+          *reinterpret_cast<uint2*>(base + tci_mask_index(tab.mk[L], x, y)) =
+              make_uint2((uint32_t)mk, (uint32_t)(mk >> 32));
+          put(L, x, y, v, mk);
+        }
+      } else if (in) {
+        const int32_t q = first[L] + y * l.w + x;
+        v = node[q];
+        mk = (uint64_t)mlo[q] | ((uint64_t)mhi[q] << 32);
+      }
+      fold_levels(tab, m.top, base, L, 3, x, y, in, lane, v, mk, put);
+    }
+    if (L + 3 >= m.top) break;
+    __syncthreads();
+  }
+  __syncthreads();
+  for (int32_t L = s + 1; L <= m.top; ++L) {
+    const tci_level l = tab.lv[L];
+    const int32_t at = first[L];
+    const float inv = 1.0f / (float)l.w;
+    for (int32_t k = threadIdx.x; k < l.w * l.h; k += kTopThreads) {
+      // (k < 2^13: half a unit over is far more than the product's rounding)
+      const int32_t j = (int32_t)(((float)k + 0.5f) * inv), i = k - j * l.w;
+      const int32_t dx = i + 1 < l.w ? 1 : 0, dy = j + 1 < l.h ? l.w : 0;
+      base[tci_tile_index(tab.wl[L], i, j)] =
+          node_merge(node_merge(node[at + k], node[at + k + dx]),
+                     node_merge(node[at + k + dy], node[at + k + dx + dy]));
+    }
+  }
 }
 
 __global__ void zero_u64_kernel(uint64_t* p, int32_t n) {
@@ -447,15 +739,47 @@ hipError_t tci_launch_update_window(const tci_map& m, uint32_t* base, int32_t L,
   return hipGetLastError();
 }
 
+bool tci_edit_tiles(int32_t n) { return n <= kTileEdits; }
+
+hipError_t tci_launch_edit_tiles(const tci_map& m, const tci_edit* edits, int32_t n,
+                                 const uint8_t* patch, uint32_t* base, int32_t max_w,
+                                 int32_t max_h, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  // a rectangle touches at most one block of cells more per axis than it
+  // fills; a short list may have rectangles of any size
+  const int64_t blocks = (int64_t)((max_w + 63) / 64 + 1) * ((max_h + 63) / 64 + 1);
+  const int32_t gy = blocks_for(blocks, 1, n < 64 ? 4096 / n : 64);
+  hipLaunchKernelGGL(edit_tiles_kernel, dim3(n, gy), dim3(kTileThreads), 0, s, m, edits, n, patch,
+                     base);
+  return hipGetLastError();
+}
+
+bool tci_update_top(const tci_map& m, int32_t s) {
+  int64_t nodes = 0;
+  for (int32_t L = s + 1; L <= m.top; ++L) nodes += (int64_t)m.lv[L].w * m.lv[L].h;
+  return s >= 1 && s < m.top && nodes <= kTopNodes;
+}
+
+hipError_t tci_launch_update_top(const tci_map& m, uint32_t* base, int32_t s, int32_t w0,
+                                 const int32_t* rects, int32_t stride, int32_t nr,
+                                 int64_t max_lanes, hipStream_t st, uint64_t* zero,
+                                 int32_t nzero) {
+  if (nr <= 0) return nzero > 0 ? tci_launch_zero_u64(zero, nzero, st) : hipSuccess;
+  const int32_t gy = blocks_for(max_lanes, kTopThreads, 64);
+  hipLaunchKernelGGL(update_top_kernel, dim3(1 + (s - w0 + 1) * nr, gy), dim3(kTopThreads), 0, st,
+                     m, base, s, w0, rects, stride, nr, zero, nzero);
+  return hipGetLastError();
+}
+
 hipError_t tci_launch_update_group(const tci_map& m, uint32_t* base, int32_t s, int32_t e,
-                                   bool wtop, const int32_t* rects, int32_t stride, int32_t nr,
-                                   int64_t max_lanes, hipStream_t st, uint64_t* zero,
+                                   int32_t w0, bool wtop, const int32_t* rects, int32_t stride,
+                                   int32_t nr, int64_t max_lanes, hipStream_t st, uint64_t* zero,
                                    int32_t nzero) {
-  if (nr <= 0 || e <= s) return nzero > 0 ? tci_launch_zero_u64(zero, nzero, st) : hipSuccess;
+  const int32_t levels = (e - s) + (e - w0) + (wtop ? 1 : 0);
+  if (nr <= 0 || levels <= 0) return nzero > 0 ? tci_launch_zero_u64(zero, nzero, st) : hipSuccess;
   const int32_t gy = blocks_for(max_lanes, 256, 64);
-  hipLaunchKernelGGL(update_group_kernel, dim3((2 * (e - s) + (wtop ? 1 : 0)) * nr, gy),
-                     dim3(256), 0, st, m, base, s, e, (int32_t)wtop, rects, stride, nr, zero,
-                     nzero);
+  hipLaunchKernelGGL(update_group_kernel, dim3(levels * nr, gy), dim3(256), 0, st, m, base, s, e,
+                     w0, (int32_t)wtop, rects, stride, nr, zero, nzero);
   return hipGetLastError();
 }
 

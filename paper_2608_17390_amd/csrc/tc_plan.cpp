@@ -64,9 +64,9 @@ constexpr int32_t kShareThreads = 8;
 bool columns_valid(const uint8_t* F, const uint8_t* B, const uint8_t* T,
                    int32_t w, int32_t h, size_t stride, int32_t* bad_x,
                    int32_t* bad_y) {
-  const int32_t hw = (int32_t)std::thread::hardware_concurrency();
-  const int32_t n = (int64_t)w * h < kShareCells ? 1 : std::max(1, std::min(hw, kShareThreads));
-  if (n == 1) return rows_valid(F, B, T, w, 0, h, stride, bad_x, bad_y);
+  if ((int64_t)w * h < kShareCells) return rows_valid(F, B, T, w, 0, h, stride, bad_x, bad_y);
+  const int32_t n =
+      std::max(1, std::min((int32_t)std::thread::hardware_concurrency(), kShareThreads));
   // bands of rows; a band whose thread cannot be started is checked here
   struct Band {
     int32_t y0, y1, bx, by;
