@@ -292,8 +292,11 @@ tc_status tc_shade_views(tc_context *ctx, const tc_view *views, int32_t n,
                                     second pass that walks 64 runs of its
                                     path per wave in parallel (4 waves by
                                     default), each from the exact state the
-                                    walk enters it with (0: no second pass;
-                                    default 120) */
+                                    walk enters it with, or as many runs as
+                                    there are lanes for if the rays are many.
+                                    A launch whose packets all run at once
+                                    hands rays over after at most 48 steps
+                                    (0: no second pass; default 120) */
 #define TC_OPT_SPLIT_QUEUE 12    /* most rays the second pass takes per call;
                                     further long rays finish in the first
                                     pass (1..2^24, default 131072; every slot
@@ -304,7 +307,9 @@ tc_status tc_shade_views(tc_context *ctx, const tc_view *views, int32_t n,
                                     into 64 runs per wave, each walked by one
                                     lane from the exact state the walk enters
                                     it with; the earliest run with a hit gives
-                                    the record (1, 2 or 4; default 4) */
+                                    the record (1, 2 or 4; default 4).  Above
+                                    1,024 rays each gets 8 to 64 lanes of one
+                                    wave instead */
 #define TC_OPT_BEAM_PASSES 17    /* render modes 0, 4 and 5: before walking,
                                     the 64 rays of each pixel packet find a
                                     common start parameter t such that none

@@ -255,6 +255,33 @@ int32_t render_counter_words(const tc_context* ctx, const ViewPlan& p) {
   return p.qcap > 0 ? 2 : 0;
 }
 
+namespace {
+
+// Steps before a ray goes to the split pass.  A launch whose packets all run
+// at once ends with its longest walk, and the split pass's waves have the
+// whole GPU after it: it hands its rays over after kSmallBudget steps at
+// most.  With more packets than that the SIMDs issue all the time, and the
+// budget stays the option's.  320x240 views: 12 + 4 us (render and pass)
+// with any budget where walks are short; where they are long 37 + 4, 24 + 8
+// and 19 + 19 us at 120, 48 and 32 steps.  Seven edits with a 640x480 view
+// each: 691, 619, 638 us in all at 120, 64 and 48, seven 320x240 views 239,
+// 239 and 221.  1920x1080 views: 127 + 22 us at 120, 101 + 98 at 48.
+constexpr int32_t kSmallBudget = 48;
+int32_t split_budget(const tc_context* ctx, const ViewPlan& p) {
+  const int64_t waves = (int64_t)ctx->num_cu * 4 * 7;   // the render's, at once
+  return p.npkt <= waves ? std::min(ctx->split_budget, kSmallBudget) : ctx->split_budget;
+}
+// Blocks of the split pass (4 / qwaves queued rays per block of 4 waves): at
+// most those that run at once (four waves a SIMD), which stride over the
+// queue; four times as many cost 0.7 us more to start over an empty queue,
+// half as many 7 us where the queue is long.
+int32_t split_blocks(const tc_context* ctx, const ViewPlan& p) {
+  return (int32_t)std::max<int64_t>(
+      1, std::min<int64_t>(ctx->num_cu * 4, ((int64_t)p.qcap * p.qwaves + 3) / 4));
+}
+
+}  // namespace
+
 hipError_t enqueue_render(tc_context* ctx, const tci_map& d, const char* dev,
                           const ViewPlan& p, void* out, hipStream_t s,
                           hipEvent_t* kev, bool* split_ran, bool counters_zeroed,
@@ -270,7 +297,7 @@ hipError_t enqueue_render(tc_context* ctx, const tci_map& d, const char* dev,
     // the traversal and kev[2..3] the split pass)
     if (split_ran) *split_ran = false;
     if (p.qcap > 0) {
-      o.split_budget = ctx->split_budget;
+      o.split_budget = split_budget(ctx, p);
       o.qcap = p.qcap;
       o.queue = queue;
       o.qcount = qctr;
@@ -279,11 +306,9 @@ hipError_t enqueue_render(tc_context* ctx, const tci_map& d, const char* dev,
     hipError_t e = tci_launch_render_inline(d, p.n, p.npkt, out, o, *inl, s,
                                             kev ? kev[0] : nullptr, kev ? kev[1] : nullptr);
     if (p.qcap > 0) {
-      const int32_t nb = (int32_t)std::max<int64_t>(
-          1, std::min<int64_t>(ctx->num_cu * 16, ((int64_t)p.qcap * p.qwaves + 3) / 4));
       if (e == hipSuccess)
-        e = tci_launch_split(d, nullptr, o, out, nb, s, inl, kev ? kev[2] : nullptr,
-                             kev ? kev[3] : nullptr);
+        e = tci_launch_split(d, nullptr, o, out, split_blocks(ctx, p), s, inl,
+                             kev ? kev[2] : nullptr, kev ? kev[3] : nullptr);
       if (split_ran) *split_ran = true;
     }
     return e;
@@ -313,7 +338,7 @@ hipError_t enqueue_render(tc_context* ctx, const tci_map& d, const char* dev,
   }
   if (p.qcap > 0) {
     uint64_t* counters = (uint64_t*)(dev + p.off_counter);
-    o.split_budget = ctx->split_budget;
+    o.split_budget = split_budget(ctx, p);
     o.qcap = p.qcap;
     o.queue = queue ? queue : (uint4*)(dev + p.off_queue);
     o.qcount = (uint32_t*)(counters + 1);
@@ -323,20 +348,19 @@ hipError_t enqueue_render(tc_context* ctx, const tci_map& d, const char* dev,
     if (e == hipSuccess)
       e = tci_launch_render(d, dv, p.n, pre, p.npkt, out, 0, o, s);
     if (e == hipSuccess) e = mark(1);
-    const int32_t nb = (int32_t)std::max<int64_t>(
-        1, std::min<int64_t>(ctx->num_cu * 16, ((int64_t)p.qcap * p.qwaves + 3) / 4));
-    // (4 / qwaves queued rays per block of 4 waves)
-    if (e == hipSuccess) e = tci_launch_split(d, dv, o, out, nb, s);
+    if (e == hipSuccess)
+      e = tci_launch_split(d, dv, o, out, split_blocks(ctx, p), s);
     if (e == hipSuccess) e = mark(2);
     if (split_ran) *split_ran = true;
     return e;
   }
+  const int32_t flat = ctx->render_mode == 1   ? 1
+                       : ctx->render_mode == 4 ? 2
+                       : ctx->render_mode == 5 ? 3
+                                               : 0;
+  const tci_voxels* vx = flat == 3 ? &ctx->vdesc : nullptr;
   hipError_t e = mark(0);
-  if (e == hipSuccess && ctx->render_mode == 5)
-    e = tci_launch_render(d, dv, p.n, pre, p.npkt, out, 3, o, s, &ctx->vdesc);
-  else if (e == hipSuccess)
-    e = tci_launch_render(d, dv, p.n, pre, p.npkt, out,
-                          ctx->render_mode == 1 ? 1 : (ctx->render_mode == 4 ? 2 : 0), o, s);
+  if (e == hipSuccess) e = tci_launch_render(d, dv, p.n, pre, p.npkt, out, flat, o, s, vx);
   if (e == hipSuccess) e = mark(1);
   return e;
 }

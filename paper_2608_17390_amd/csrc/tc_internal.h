@@ -156,10 +156,11 @@ hipError_t tci_launch_march(const tci_map& m, const tci_view* views,
                             int32_t nviews, const int64_t* pkt_prefix,
                             int64_t npkt, void* out, const tci_render_opts& o,
                             hipStream_t s);
-// Second pass of a hierarchical render: walk every queued long ray as 64
-// segments in parallel, one wave per ray.
+// Second pass of a hierarchical render: walk every queued long ray as runs
+// of its path in parallel.
 // With ev_start / ev_stop, the kernel records its own start and end in them
-// (the events travel with its dispatch instead of as markers on the stream).
+// (the events travel with its dispatch instead of as markers on the stream;
+// calls with t only).
 hipError_t tci_launch_split(const tci_map& m, const tci_view* views,
                             const tci_render_opts& o, void* out, int32_t nblocks,
                             hipStream_t s, const tci_inline* t = nullptr,

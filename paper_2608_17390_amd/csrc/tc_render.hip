@@ -31,8 +31,8 @@ __device__ __forceinline__ int32_t lane_now() {
 // pyramid *vx instead (render mode 5, the voxel-accelerated march).
 // kCount: the launch counts the nodes and cells its rays read (o.count);
 // the production instance keeps no counter through the walk.
-// kBoost: the launch has a priority boost (o.boost; the hierarchical mode,
-// whose walk is instantiated for it).
+// kBoost: the launch may have a priority boost (o.boost; the hierarchical
+// mode's walk is instantiated without).
 template <bool kFlat, bool kOcc, bool kCount, bool kVox = false, bool kBoost = false>
 __device__ __forceinline__ void render_body(
     const tci_map& m, const tci_view* __restrict__ views, int32_t nviews,
@@ -41,6 +41,8 @@ __device__ __forceinline__ void render_body(
   __shared__ lvl_t lv[TCI_MAX_LEVELS];
   __shared__ uint32_t woff[TCI_MAX_LEVELS];
   __shared__ uint32_t moff[kOcc ? TCI_MAX_LEVELS : 1];
+  __shared__ uint4 vrec[kVox ? TCI_MAX_LEVELS : 1];
+  if constexpr (kVox) load_voxel_levels(*vx, vrec);
   load_levels_beam(m, lv, woff, kOcc ? moff : nullptr);
   // clear the queue counter the next render of this ring slot will use
   // (its last user finished before this launch)
@@ -77,25 +79,21 @@ __device__ __forceinline__ void render_body(
   if (r.Dx == 0 && r.Dy == 0) {
     trace_vertical(m, lv, r, word, depth);
     if (kCount && beam_reads) atomicAdd(o.count, (unsigned long long)beam_reads);
-  } else if constexpr (kFlat || kOcc || kVox) {
+  } else if constexpr (kFlat) {
     walk_t s;
     walk_idx_t k;
-    const int32_t top = kFlat ? 0 : m.top;
-    start_walk(r, k, s, t_start, kFlat ? 0 : clamp_level(o.start_level, top), m.W, m.H);
-    s.reads = beam_reads;
+    walk_origin(r, k);
+    walk_at_origin(r, 0, s);
     uint32_t col = 0;
-    const int32_t Lmax = kFlat ? 0 : clamp_level(o.max_level, top);
     const int32_t boost = __builtin_amdgcn_readfirstlane(o.boost);
     // the walk runs a loop specialised to the sign of the ray's vertical
     // direction (a packet's rays mostly share it; a wave holding both signs
     // runs the two loops one after the other)
     int32_t st;
     if (r.Dz < 0)
-      st = walk_steps<false, kOcc, false, 1, kVox>(m, lv, r, k, s, Lmax, kIterCap + 1, col, boost,
-                                                   0, 0, 0, moff, kCount, vx);
+      st = walk_steps<false, 1>(m, lv, r, k, s, 0, kIterCap + 1, col, boost, kCount);
     else
-      st = walk_steps<false, kOcc, false, 2, kVox>(m, lv, r, k, s, Lmax, kIterCap + 1, col, boost,
-                                                   0, 0, 0, moff, kCount, vx);
+      st = walk_steps<false, 2>(m, lv, r, k, s, 0, kIterCap + 1, col, boost, kCount);
     if (st == kWalking) st = kCapped;   // the whole budget ran out (never expected)
     // the origin is needed again only here: recompute it from the view
     // rather than keep it in registers through the walk (the lane index is
@@ -104,6 +102,7 @@ __device__ __forceinline__ void render_body(
     finish(r, s, m.W, st, col, word, depth);
     if (kCount) atomicAdd(o.count, (unsigned long long)s.reads);
   } else {
+    constexpr int kTest = kOcc ? kMasks : kVox ? kVoxels : kMinMax;
     const int32_t Lmax = clamp_level(o.max_level, m.top);
     const int32_t boost = __builtin_amdgcn_readfirstlane(o.boost);
     // the budget bounds the walk: at most the split budget, or without a
@@ -130,7 +129,8 @@ __device__ __forceinline__ void render_body(
     int32_t reads = beam_reads, st;
     for (;;) {
       const int32_t budget = split ? o.split_budget : kIterCap + 1;
-      st = skim_walk<kBoost>(m, lv, f, s, Lmax, budget, boost, reads, kCount, ray, oz, word, depth);
+      st = skim_walk<kBoost, kTest>(m, lv, f, s, Lmax, budget, boost, reads, kCount, ray, oz, word,
+                                    depth, skim_test{moff, vx, vrec});
       if (!split) break;
       split = false;
       // long walks go to the split pass, as many as the queue holds
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(64 * kPackets)
 void render_occ_kernel(tci_map m, const tci_view* __restrict__ views, int32_t nviews,
                        const int64_t* __restrict__ pkt_prefix, int64_t npkt, void* out,
                        tci_render_opts o) {
-  render_body<false, true, kCount>(m, views, nviews, pkt_prefix, o.rows, npkt, out, o);
+  render_body<false, true, kCount, false, true>(m, views, nviews, pkt_prefix, o.rows, npkt, out, o);
 }
 
 template <bool kCount>
@@ -215,8 +215,8 @@ __global__ __launch_bounds__(64 * kPackets)
 void render_vox_kernel(tci_map m, const tci_view* __restrict__ views, int32_t nviews,
                        const int64_t* __restrict__ pkt_prefix, int64_t npkt, void* out,
                        tci_render_opts o, tci_voxels vx) {
-  render_body<false, false, kCount, true>(m, views, nviews, pkt_prefix, o.rows, npkt, out, o,
-                                          &vx);
+  render_body<false, false, kCount, true, true>(m, views, nviews, pkt_prefix, o.rows, npkt, out,
+                                                o, &vx);
 }
 
 // Dominant-axis cell line where the ray leaves the map's columns, or rises
@@ -235,6 +235,120 @@ __device__ __forceinline__ int32_t exit_line(const ray_t& r, const tci_map& m,
   const double c = axis == 0 ? ((double)r.Ox + t * r.Dx) / S : ((double)r.Oy + t * r.Dy) / S;
   const double lim = axis == 0 ? (double)m.W : (double)m.H;
   return (int32_t)floor(fmin(fmax(c, -1.0), lim));
+}
+
+// Rays up to which the split pass gives each ray its whole waves and cells
+// (below); with more, each gets some lanes of a wave and the pyramid
+// (split_runs).  On full-HD views: 300 rays 8.0 us with whole waves and 12.9
+// with a share of lanes, 1,000 to 2,000 rays about 10 either way, 5,000 rays
+// 42 and 22, 25,000 rays 370 and 73.
+constexpr uint32_t kFlatRays = 1024;
+
+// The split pass for a long queue: G = 8, 16, 32 or 64 lanes of a wave per
+// ray.  The remaining path is cut into G runs whose lengths grow with the
+// distance (boundary j at (j / G)^3 of the lines: most of these rays end
+// soon), lane j walks run j in single precision with the pyramid
+// (skim_steps), in chunks of 16 steps; the earliest run with a hit gives the
+// record, the runs after it stop.
+__device__ __forceinline__ void split_runs(const tci_map& m, const lvl_t* lv,
+                                           const tci_view* __restrict__ views, void* out,
+                                           const tci_render_opts& o, uint32_t n, int32_t lgG) {
+  const int32_t lane = threadIdx.x & 63, G = 1 << lgG;
+  const uint32_t per = 64u >> lgG;                       // rays of a wave
+  const int32_t j = lane & (G - 1);
+  const uint64_t group = (G == 64 ? ~0ull : (1ull << G) - 1) << (lane & ~(G - 1));
+  const int32_t Lmax = clamp_level(o.max_level, m.top);
+  const uint32_t waves = gridDim.x * 4;
+  for (uint32_t w = blockIdx.x * 4 + (threadIdx.x >> 6); w * per < n; w += waves) {
+    const uint32_t e = w * per + ((uint32_t)lane >> lgG);
+    int32_t st = kSegEnd;
+    uint32_t word = kMiss;
+    float depth = __builtin_inff();
+    const uint4 q = o.queue[min(e, n - 1)];
+    const tci_view& v = views[q.x];
+    const int32_t px = (int32_t)(q.y % (uint32_t)v.w), py = (int32_t)(q.y / (uint32_t)v.w);
+    ray_t r;
+    pixel_ray(v, px, py, r);
+    skim_ray f;
+    skim_init(r, f);
+    skim_t s;
+    const bool ax = r.ax >= r.ay;
+    const bool fwd = (ax ? r.Dx : r.Dy) > 0;
+    const int32_t c0 = (int32_t)q.z, dir = fwd ? 1 : -1;
+    const int32_t N = max(1, (exit_line(r, m, ax ? 0 : 1) - c0) * dir + 1);
+    auto bound = [&](int32_t k) {
+      const float u = (float)k / (float)G;
+      return c0 + dir * min(N, max(k, (int32_t)((float)N * (u * u * u))));
+    };
+    const int32_t b0 = bound(j), b1 = j == G - 1 ? (fwd ? INT32_MAX : INT32_MIN) : bound(j + 1);
+    auto ray = [&]() {
+      return skim_int{(int32_t)r.Ox, (int32_t)r.Oy, (int32_t)r.Oz, r.Dx, r.Dy, r.Dz};
+    };
+    auto oz = [&]() { return (int32_t)r.Oz; };
+    if (e < n && b0 != b1) {
+      st = kWalking;
+      // the cell the ray enters line b0 in (the origin's cell, if that is
+      // on it or beyond)
+      const int32_t oc = ax ? f.cx : f.cy;
+      s.L = 0;
+      if ((b0 - oc) * dir <= 0) {
+        s.x = f.cx;
+        s.y = f.cy;
+        s.zin = r.Dz < 0 ? f.zhi : f.zlo;
+      } else {
+        const float t = ((float)(b0 + (fwd ? 0 : 1) - oc) - (ax ? f.fx : f.fy)) * (ax ? f.rx : f.ry);
+        const float p = fmaf(t, ax ? f.dy : f.dx, ax ? f.fy : f.fx);
+        int32_t c = (int32_t)floorf(p) + (ax ? f.cy : f.cx);
+        if (__builtin_expect(!skim_sure(p), 0)) {
+          ray_t r2 = r;
+          walk_idx_t k;
+          walk_t wk;
+          walk_origin(r2, k);
+          walk_at_line(r2, k, wk, ax ? 0 : 1, b0);
+          c = ax ? wk.nj : wk.ni;
+        }
+        s.x = ax ? b0 : c;
+        s.y = ax ? c : b0;
+        s.zin = fmaf(t, f.dz, r.Dz < 0 ? f.zhi : f.zlo);
+      }
+    }
+    int32_t it = 0, reads = 0;
+    uint32_t col = 0;
+    float ze = 0.0f;
+    for (;;) {
+      const uint64_t hit = __ballot(st == kHitCell) & group;
+      if (st == kWalking && hit && lane > __ffsll((unsigned long long)hit) - 1) st = kSegEnd;
+      if (!__ballot(st == kWalking)) break;
+      if (st != kWalking) continue;
+      const int32_t stop = it + 16;
+      if (r.Dz < 0)
+        st = skim_steps<1, kMinMax, true>(m, lv, f, s, Lmax, stop, it, col, ze, reads,
+                                          o.count != nullptr, ray, skim_test{}, ax, b1);
+      else
+        st = skim_steps<2, kMinMax, true>(m, lv, f, s, Lmax, stop, it, col, ze, reads,
+                                          o.count != nullptr, ray, skim_test{}, ax, b1);
+      if (st == kHitCell && !skim_sure_hit(f, s, col, ze, m.W, oz, word, depth)) {
+        const skim_cell c = skim_exact_cell(ray(), s.x, s.y, col, m.W);
+        if (c.hit) {
+          word = c.word;
+          depth = __uint_as_float(c.depth);
+        } else {
+          skim_step_whole(f, s, ray());
+          ++it;
+          st = kWalking;
+        }
+      }
+      if (st == kWalking && it > kIterCap) {   // (never expected)
+        st = kHitCell;
+        word = kStuck;
+        depth = __builtin_nanf("");
+      }
+    }
+    if (o.count) atomicAdd(o.count, (unsigned long long)reads);
+    const uint64_t hit = __ballot(st == kHitCell) & group;
+    const int32_t first = hit ? __ffsll((unsigned long long)hit) - 1 : (lane & ~(G - 1));
+    if (e < n && lane == first) tcp::store_hit(out, v.out_base + q.y, word, depth);
+  }
 }
 
 // Split pass: G = split_waves (1, 2 or 4) waves of one block per queued
@@ -264,6 +378,11 @@ __device__ __forceinline__ void split_body(const tci_map& m,
   const uint32_t grp = (uint32_t)wave / G, g = (uint32_t)wave - grp * G;
   const int32_t lgR = 6 + (G == 4 ? 2 : (G == 2 ? 1 : 0));   // 64 G runs per ray
   const uint32_t n = min(*o.qcount, o.qcap);
+  if (n > kFlatRays) {
+    // as many lanes per ray as about 2^18 in flight allow
+    split_runs(m, lv, views, out, o, n, n <= 4096 ? 6 : n <= 8192 ? 5 : n <= 16384 ? 4 : 3);
+    return;
+  }
   const lvl_t l0 = lv[0];
   for (uint32_t e0 = blockIdx.x * per; e0 < n; e0 += gridDim.x * per) {
     const uint32_t e = e0 + grp;
@@ -354,15 +473,15 @@ __device__ __forceinline__ void split_body(const tci_map& m,
   }
 }
 
-__global__ __launch_bounds__(256) void split_kernel(tci_map m,
-                                                    const tci_view* __restrict__ views,
-                                                    void* out, tci_render_opts o) {
+// (at most 128 VGPRs: four waves per SIMD)
+__global__ __launch_bounds__(256, 4) void split_kernel(tci_map m,
+                                                       const tci_view* __restrict__ views,
+                                                       void* out, tci_render_opts o) {
   split_body(m, views, out, o);
 }
-
 // The split pass of a render whose tables came in the kernel's arguments.
-__global__ __launch_bounds__(256) void split_inline_kernel(tci_map m, void* out,
-                                                           tci_render_opts o, tci_inline t) {
+__global__ __launch_bounds__(256, 4) void split_inline_kernel(tci_map m, void* out,
+                                                              tci_render_opts o, tci_inline t) {
   split_body(m, (const tci_view*)(const char*)t.words, out, o);
 }
 
@@ -442,7 +561,7 @@ __global__ __launch_bounds__(256) void render_persistent_kernel(
     if (drained && __ballot(active) == 0) break;
     int32_t st = kWalking;
     uint32_t col = 0;
-    if (active) st = walk_steps(m, lv, r, k, s, Lmax, iters, col);
+    if (active) st = walk_steps<>(m, lv, r, k, s, Lmax, iters, col);
     if (st != kWalking) {
       uint32_t word;
       float depth;

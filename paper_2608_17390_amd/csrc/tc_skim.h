@@ -183,32 +183,107 @@ __device__ __forceinline__ skim_cell skim_exact_cell(skim_int q, int32_t x, int3
   return skim_cell{hit ? 1 : 0, word, __float_as_uint(depth)};
 }
 
+// Does voxel column (X, Y) of level k of the voxel occupancy pyramid hold a
+// set bit over heights [zl, zh]?  The heights are the ray's range over the
+// column, already widened to cover their rounding; both ends are clipped into the pyramid's heights, so a range
+// partly or wholly below height 0 tests the first voxel, which every
+// in-map column's floor (unbounded below) sets, and a range wholly above
+// the top (z > 256) holds nothing.
+// Per 8-voxel tile in z, the column's eight bits sit in four words (two
+// 64-bit loads): in-tile Morton index x0 y0 z0 x1 y1 | z1 x2 y2 z2 puts
+// z0 in the bit and z1, z2 in the word.  `reads` counts the loads.
+// `l` is the level's record (load_voxel_levels).
+__device__ __forceinline__ bool voxel_range(const uint32_t* base, const uint4 l, int32_t vz_log2,
+                                            int32_t X, int32_t Y, float zl, float zh,
+                                            int32_t& reads) {
+  const float inv = __builtin_amdgcn_ldexpf(1.0f, -vz_log2);
+  const int32_t z0 = (int32_t)floorf(fmaxf(zl * inv, 0.0f));
+  const int32_t z1 = min((int32_t)floorf(__builtin_amdgcn_fmed3f(zh * inv, 0.0f, 1024.0f)),
+                         (int32_t)l.w - 1);
+  if (z0 > z1) return false;
+  const uint32_t x = (uint32_t)X & 7, y = (uint32_t)Y & 7;
+  const uint32_t sh = (x & 1) | ((y & 1) << 1) | ((x & 2) << 2) | ((y & 2) << 3);
+  const uint32_t col = l.x + (((uint32_t)(Y >> 3) * l.y + (uint32_t)(X >> 3)) << 4) +
+                       (((x >> 2) << 1) | (y & 4));
+  for (int32_t tz = z0 >> 3; tz <= (z1 >> 3); ++tz) {
+    const uint32_t* t = base + col + (uint32_t)tz * l.z;
+    const uint2 a = *reinterpret_cast<const uint2*>(t);
+    const uint2 b = *reinterpret_cast<const uint2*>(t + 8);
+    reads += 2;
+    // two bits of each word: z0 in bits 0 and 4 above sh
+    auto two = [&](uint32_t w) {
+      const uint32_t c = w >> sh;
+      return (c | (c >> 3)) & 3u;
+    };
+    const uint32_t bits = two(a.x) | (two(a.y) << 2) | (two(b.x) << 4) | (two(b.y) << 6);
+    const int32_t lo = max(z0 - tz * 8, 0), hi = min(z1 - tz * 8, 7);
+    const uint32_t want = ((2u << hi) - 1u) & ~((1u << lo) - 1u);
+    if (bits & want) return true;
+  }
+  return false;
+}
+
+// The voxel levels' records in LDS, one 16-byte read a step: the level's
+// offset, tiles per row, words from a tile to the one above, and voxels in
+// height.
+__device__ __forceinline__ void load_voxel_levels(const tci_voxels& vx, uint4* rec) {
+  if (threadIdx.x < TCI_MAX_LEVELS) {
+    const tci_vlevel& l = vx.lv[threadIdx.x];
+    rec[threadIdx.x] = make_uint4(l.off, (uint32_t)l.tiles_x,
+                                  (uint32_t)(l.tiles_y * l.tiles_x) << 4, (uint32_t)l.nz);
+  }
+  __syncthreads();
+}
+
 // Walk until a cell that may hold the hit (kHitCell, its column in col), a
 // certain miss (kMissed), or step number `budget` (kWalking); `it` counts the
 // steps, over several calls.  ze is the height at which the ray leaves that
 // cell, moved by the margin to the other side than zin.  ray() gives the ray again for a step that is taken in whole
 // numbers, so that no register holds its integers through the walk.
 // kDir: 1 Dz < 0, 2 otherwise.
-template <int kDir, class RayFn>
+// kTest: what a node above the cells is tested against.  kMinMax: its
+// min/max pyramid node.  kMasks: a node that only the slab test keeps, also
+// its occupancy mask (t.moff: the mask levels' word offsets): the ray's
+// heights over the node must meet an occupied band, or the ray passes between
+// the node's slabs.  kVoxels: the voxel occupancy pyramid *t.vx (Section
+// 3.2) instead: a node of level L >= the voxels' footprint level Lv is voxel
+// column (ni, nj) of voxel level L - Lv; nodes below Lv are always descended
+// (the leaf voxel's cells are then tested one by one), and a climb from below
+// Lv goes straight to Lv, when the step left the leaf voxel.
+enum { kMinMax = 0, kMasks = 1, kVoxels = 2 };
+struct skim_test {
+  const uint32_t* moff;
+  const tci_voxels* vx;
+  const uint4* vrec;       // the voxel levels' records, in LDS
+};
+// With kSeg the walk also ends (kSegEnd) once it enters a cell at or beyond
+// line seg_end of axis seg_x (x or y), in the ray's direction.
+template <int kDir, int kTest = kMinMax, bool kSeg = false, class RayFn>
 __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
                                               const skim_ray& f, skim_t& s, int32_t max_level,
                                               int32_t budget, int32_t& it, uint32_t& col,
                                               float& ze_out, int32_t& reads, bool count,
-                                              RayFn ray) {
+                                              RayFn ray, const skim_test& t = skim_test{},
+                                              bool seg_x = false, int32_t seg_end = 0) {
   const bool desc = kDir == 1;
   const bool fx = f.dx >= 0.0f, fy = f.dy >= 0.0f;
   const int32_t nx1 = fx ? 1 : 0, ny1 = fy ? 1 : 0;
   const float m2 = f.zhi - f.zlo;
   for (; it < budget; ++it) {
+    if constexpr (kSeg) {
+      const int32_t c = seg_x ? s.x : s.y;
+      if ((seg_x ? fx : fy) ? c >= seg_end : c <= seg_end) return kSegEnd;
+    }
     const int32_t L = s.L;
     const uint4 lq = *reinterpret_cast<const uint4*>(&lv[L]);
     const int32_t w1 = (int32_t)lq.y, h1 = (int32_t)lq.z;
     const int32_t ni = s.x >> L, nj = s.y >> L;
     const bool inmap = ((uint32_t)ni <= (uint32_t)w1) & ((uint32_t)nj <= (uint32_t)h1);
-    if (count) reads += inmap ? 1 : 0;
+    const bool node = kTest != kVoxels || L == 0;   // tested against its word
+    if (count) reads += (inmap & node) ? 1 : 0;
     const uint32_t ci = (uint32_t)clamp0(ni, w1), cj = (uint32_t)clamp0(nj, h1);
-    const uint32_t v = map_word(m.base, lq.x + ((umul24(cj >> 3, lq.w) + (ci >> 3)) << 6) +
-                                            ((cj & 7) << 3) + (ci & 7));
+    const uint32_t at = ((umul24(cj >> 3, lq.w) + (ci >> 3)) << 6) + ((cj & 7) << 3) + (ci & 7);
+    const uint32_t v = map_word(m.base, lq.x + at);
     // times of the crossings through the far faces
     const int32_t gx = (ni + nx1) << L, gy = (nj + ny1) << L;
     const float tx = ((float)(gx - f.cx) - f.fx) * f.rx;
@@ -217,8 +292,29 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
     const float te = fminf(tx, ty);
     const float ze = fmaf(te, f.dz, desc ? f.zlo : f.zhi);
     const float lo = desc ? ze : s.zin, hi = desc ? s.zin : ze;
-    const bool occ = inmap & ((lo <= (float)(v & 0xFF)) |
-                              ((lo <= (float)((v >> 16) & 0xFF)) & (hi >= (float)((v >> 8) & 0xFF))));
+    bool occ = inmap & ((lo <= (float)(v & 0xFF)) |
+                        ((lo <= (float)((v >> 16) & 0xFF)) & (hi >= (float)((v >> 8) & 0xFF))));
+    if constexpr (kTest == kMasks) {
+      if (occ && L > 0 && !(lo <= (float)(v & 0xFF))) {
+        const uint2 mw = *reinterpret_cast<const uint2*>(m.base + t.moff[L] + 2 * at);
+        if (count) reads += 2;
+        const uint64_t mask = (uint64_t)mw.x | ((uint64_t)mw.y << 32);
+        const int32_t kl = min(max((int32_t)floorf(lo * 0.25f), 0), 63);
+        const int32_t kh = min(max((int32_t)floorf(hi * 0.25f), 0), 63);
+        occ = (mask & (~0ull >> (63 - kh)) & (~0ull << kl)) != 0;
+      }
+    }
+    if constexpr (kTest == kVoxels) {
+      if (L > 0) {
+        const int32_t Lv = t.vx->v_log2;
+        occ = inmap;
+        if (inmap && L >= Lv) {
+          int32_t vr = 0;
+          occ = voxel_range(t.vx->base, t.vrec[L - Lv], t.vx->vz_log2 + L - Lv, ni, nj, lo, hi, vr);
+          if (count) reads += vr;
+        }
+      }
+    }
     if (occ) {
       if (L == 0) {
         col = v;
@@ -245,7 +341,9 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
         zn = fmaf(n.ex ? tx : ty, f.dz, desc ? f.zhi : f.zlo);
       }
       // go up one level when the step entered a new parent node
-      s.L = L + (((L < max_level) & (((uint32_t)((s.x ^ x) | (s.y ^ y)) >> L) > 1u)) ? 1 : 0);
+      int32_t up = 1;
+      if constexpr (kTest == kVoxels) up = max(min(t.vx->v_log2, max_level) - L, 1);
+      s.L = L + (((L < max_level) & (((uint32_t)((s.x ^ x) | (s.y ^ y)) >> (L + up - 1)) > 1u)) ? up : 0);
       s.x = x;
       s.y = y;
       s.zin = zn;
@@ -318,23 +416,23 @@ __device__ __forceinline__ void skim_step_whole(const skim_ray& f, skim_t& s, co
 // kMissed, or kWalking when the budget ran out).  With kBoost a wave raises
 // its issue priority after boost, 2 boost and 4 boost steps (an instance of
 // its own: the stops cost the walk 1.4 %).
-template <bool kBoost, class RayFn, class OzFn>
+template <bool kBoost, int kTest, class RayFn, class OzFn>
 __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
                                              const skim_ray& f, skim_t& s, int32_t max_level,
                                              int32_t budget, int32_t boost, int32_t& reads,
                                              bool count, RayFn ray, OzFn oz, uint32_t& word,
-                                             float& depth) {
+                                             float& depth, const skim_test& t) {
   int32_t it = 0;
   uint32_t col = 0;
   float ze = 0.0f;
   const bool down = f.dz < 0.0f;
-  int32_t stop = kBoost ? min(boost, budget) : budget;
+  int32_t stop = kBoost && boost > 0 ? min(boost, budget) : budget;
   for (;;) {
     int32_t st;
     if (down)
-      st = skim_steps<1>(m, lv, f, s, max_level, stop, it, col, ze, reads, count, ray);
+      st = skim_steps<1, kTest>(m, lv, f, s, max_level, stop, it, col, ze, reads, count, ray, t);
     else
-      st = skim_steps<2>(m, lv, f, s, max_level, stop, it, col, ze, reads, count, ray);
+      st = skim_steps<2, kTest>(m, lv, f, s, max_level, stop, it, col, ze, reads, count, ray, t);
     if (kBoost && stop < budget && st == kWalking) {
       if (stop == boost) __builtin_amdgcn_s_setprio(1);
       else if (stop == 2 * boost) __builtin_amdgcn_s_setprio(2);

@@ -483,46 +483,6 @@ __device__ __forceinline__ int32_t far_index(int32_t n, int32_t L, int32_t f, in
   return __mul24(s, (n + f) << L) + off;
 }
 
-// Does voxel column (X, Y) of level k of the voxel occupancy pyramid hold a
-// set bit over heights [zl, zh]?  The heights are float estimates of the
-// ray's exact range over the column, already widened to cover their
-// rounding; both ends are clipped into the pyramid's heights, so a range
-// partly or wholly below height 0 tests the first voxel, which every
-// in-map column's floor (unbounded below) sets, and a range wholly above
-// the top (z > 256) holds nothing.
-// Per 8-voxel tile in z, the column's eight bits sit in four words (two
-// 64-bit loads): in-tile Morton index x0 y0 z0 x1 y1 | z1 x2 y2 z2 puts
-// z0 in the bit and z1, z2 in the word.  `reads` counts the loads.
-__device__ __forceinline__ bool voxel_range(const tci_voxels& vx, int32_t k, int32_t X,
-                                            int32_t Y, float zl, float zh, int32_t& reads) {
-  const tci_vlevel& l = vx.lv[k];
-  const float inv = __builtin_amdgcn_ldexpf(1.0f, -(vx.vz_log2 + k));
-  const int32_t z0 = max((int32_t)floorf(fmaxf(zl, -1.0f) * inv), 0);
-  const int32_t z1 = min(max((int32_t)floorf(fmaxf(fminf(zh, 1.0e6f), -1.0f) * inv), 0),
-                         l.nz - 1);
-  if (z0 > z1) return false;
-  const uint32_t x = (uint32_t)X & 7, y = (uint32_t)Y & 7;
-  const uint32_t wb = ((x >> 2) << 1) | ((y >> 2) << 2);
-  const uint32_t sh = (x & 1) | ((y & 1) << 1) | (((x >> 1) & 1) << 3) | (((y >> 1) & 1) << 4);
-  const uint32_t* col = vx.base + l.off +
-                        (uint32_t)(((Y >> 3) * l.tiles_x + (X >> 3)) << 4) + wb;
-  const uint32_t zstride = (uint32_t)(l.tiles_y * l.tiles_x) << 4;
-  for (int32_t tz = z0 >> 3; tz <= (z1 >> 3); ++tz) {
-    const uint32_t* t = col + (uint32_t)tz * zstride;
-    const uint2 a = *reinterpret_cast<const uint2*>(t);
-    const uint2 b = *reinterpret_cast<const uint2*>(t + 8);
-    reads += 2;
-    const uint32_t bits = ((a.x >> sh) & 1u) | (((a.x >> (sh + 4)) & 1u) << 1) |
-                          (((a.y >> sh) & 1u) << 2) | (((a.y >> (sh + 4)) & 1u) << 3) |
-                          (((b.x >> sh) & 1u) << 4) | (((b.x >> (sh + 4)) & 1u) << 5) |
-                          (((b.y >> sh) & 1u) << 6) | (((b.y >> (sh + 4)) & 1u) << 7);
-    const int32_t lo = max(z0 - tz * 8, 0), hi = min(z1 - tz * 8, 7);
-    const uint32_t want = ((2u << hi) - 1u) & ~((1u << lo) - 1u);
-    if (bits & want) return true;
-  }
-  return false;
-}
-
 // Advance the walk by up to `budget` iterations.  Returns kWalking if the
 // budget ran out, else the final state; on kHitCell, `col` holds the
 // column of the current cell (s.ni, s.nj at level 0).  k holds the ray's
@@ -531,38 +491,19 @@ __device__ __forceinline__ bool voxel_range(const tci_voxels& vx, int32_t k, int
 // issue priority after boost, 2*boost and 4*boost iterations: the few long
 // walks of a launch, which otherwise trail it, then win issue slots over
 // the many short ones sharing their SIMD.
-// With kSeg the walk also stops (kSegEnd) once its node lies wholly
-// outside the cell lines [seg_lo, seg_hi] of axis seg_axis (0 x, 1 y).
 // With kCap every call counts the walk's iterations in s.iters and stops
 // (kCapped) past kIterCap, a guard for callers that resume a walk without
 // bound; a caller whose budget already bounds the walk passes false.  With
 // count false, s.reads is left alone.
-// With kOcc, a node that only the slab test keeps is also tested against
-// its occupancy mask (moff: the mask levels' word offsets, in LDS): the
-// ray's height range over the node, widened by two units to cover the
-// rounding of its float estimate, must meet an occupied band, or the ray
-// passes between the node's slabs and the node is skipped.
 // kDir fixes the sign of the ray's vertical direction for callers that know
 // it for every lane of the wave (1: Dz < 0, 2: Dz >= 0; 0: read it per ray),
 // so the loop carries no per-lane selects on it.
-// With kVox (the voxel-accelerated march, Section 3.2), nodes above the
-// cells are tested against the voxel occupancy pyramid *vx instead of the
-// min/max pyramid: a node of level L >= the voxels' footprint level Lv is
-// voxel column (ni, nj) of voxel level L - Lv, empty over the ray's height
-// range over the node (widened by two units to cover the rounding of its
-// float estimate) or not; nodes below Lv are always descended (the leaf
-// voxel's cells are then tested exactly, one by one).
-template <bool kSeg = false, bool kOcc = false, bool kCap = true, int kDir = 0,
-          bool kVox = false>
+template <bool kCap = true, int kDir = 0>
 __device__ __forceinline__ int32_t walk_steps(const tci_map& m, const lvl_t* lv,
                                               const ray_t& r, const walk_idx_t& k, walk_t& s,
                                               int32_t max_level, int32_t budget,
                                               uint32_t& col, int32_t boost = 0,
-                                              int32_t seg_axis = 0,
-                                              int32_t seg_lo = 0, int32_t seg_hi = 0,
-                                              const uint32_t* moff = nullptr,
-                                              bool count = true,
-                                              const tci_voxels* vx = nullptr) {
+                                              bool count = true) {
   const bool desc = kDir == 1 ? true : (kDir == 2 ? false : r.Dz < 0);
   const bool fx = r.Dx > 0, fy = r.Dy > 0;
   const int32_t sx = fx ? 1 : -1, sy = fy ? 1 : -1;
@@ -578,10 +519,6 @@ __device__ __forceinline__ int32_t walk_steps(const tci_map& m, const lvl_t* lv,
       if (++s.iters > kIterCap) return kCapped;
     }
     const int32_t L = s.L;
-    if (kSeg) {
-      const int32_t n = seg_axis == 0 ? s.ni : s.nj;
-      if ((n << L) > seg_hi || ((n + 1) << L) - 1 < seg_lo) return kSegEnd;
-    }
     // the level's record in one 16-byte LDS read, then every lane loads its
     // node clamped into the level, with no branch around the load: the
     // step's chain holds one LDS round trip and no exec-mask branch before
@@ -594,13 +531,13 @@ __device__ __forceinline__ int32_t walk_steps(const tci_map& m, const lvl_t* lv,
     l.h1 = (int32_t)lq.z;
     l.tiles_x = (int32_t)lq.w;
     const bool inmap = ((uint32_t)s.ni <= (uint32_t)l.w1) & ((uint32_t)s.nj <= (uint32_t)l.h1);
-    if (count) s.reads += (inmap & (!kVox | (L == 0))) ? 1 : 0;
+    if (count) s.reads += inmap ? 1 : 0;
     const uint32_t ci = (uint32_t)clamp0(s.ni, l.w1);
     const uint32_t cj = (uint32_t)clamp0(s.nj, l.h1);
     const uint32_t vraw = map_word(m.base, l.off + ((umul24(cj >> 3, (uint32_t)l.tiles_x) +
                                                      (ci >> 3)) << 6) +
                                                ((cj & 7) << 3) + (ci & 7));
-    const uint32_t v = (inmap & (!kVox | (L == 0))) ? vraw : 0u;
+    const uint32_t v = inmap ? vraw : 0u;
     // keys and heights of the crossings through the node's far faces
     const int32_t ix = far_index(s.ni, L, nx1, sx, k.offx);
     const int32_t iy = far_index(s.nj, L, ny1, sy, k.offy);
@@ -619,36 +556,6 @@ __device__ __forceinline__ int32_t walk_steps(const tci_map& m, const lvl_t* lv,
       const uint32_t a = v & 0xFF, b = (v >> 8) & 0xFF, c = (v >> 16) & 0xFF;
       // the three compares combined without short-circuit branches
       occ = (lo <= hmul(a, Dlo)) | ((lo <= hmul(c, Dlo)) & (hi >= hmul(b, Dhi)));
-      if constexpr (kOcc) {
-        if (occ && L > 0 && !(lo <= hmul(a, Dlo))) {
-          const uint32_t mi = moff[L] +
-                              ((__umul24((uint32_t)s.nj >> 3, (uint32_t)l.tiles_x) +
-                                ((uint32_t)s.ni >> 3)) << 7) +
-                              ((((uint32_t)(s.nj & 7) << 3) + (uint32_t)(s.ni & 7)) << 1);
-          const uint2 mw = *reinterpret_cast<const uint2*>(m.base + mi);
-          const uint64_t mask = (uint64_t)mw.x | ((uint64_t)mw.y << 32);
-          if (count) s.reads += 2;
-          const float zl = (float)lo / (float)Dlo - 2.0f;
-          const float zh = (float)hi / (float)Dhi + 2.0f;
-          const int32_t kl = min(max((int32_t)floorf(zl * 0.25f), 0), 63);
-          const int32_t kh = min(max((int32_t)floorf(zh * 0.25f), 0), 63);
-          const uint64_t range = (~0ull >> (63 - kh)) & (~0ull << kl);
-          occ = (mask & range) != 0;
-        }
-      }
-      if constexpr (kVox) {
-        if (L > 0) {
-          const int32_t Lv = vx->v_log2;
-          occ = true;
-          if (L >= Lv) {
-            const float zl = (float)lo / (float)Dlo - 2.0f;
-            const float zh = (float)hi / (float)Dhi + 2.0f;
-            int32_t vr = 0;
-            occ = voxel_range(*vx, L - Lv, s.ni, s.nj, zl, zh, vr);
-            if (count) s.reads += vr;
-          }
-        }
-      }
     }
     if (occ && L == 0) {
       col = v;
@@ -692,20 +599,10 @@ __device__ __forceinline__ int32_t walk_steps(const tci_map& m, const lvl_t* lv,
       if (away | above) return kMissed;
       // go up one level when the step entered a new parent node
       nL = L;
-      int32_t up = 1;
-      if constexpr (kVox) {
-        // below the voxels' footprint level every node counts as occupied,
-        // so a climb stops there only to descend again: inside a leaf
-        // voxel the walk stays on the cells, and the step that leaves it
-        // climbs straight to the footprint level (the new leaf voxel is
-        // entered at this very crossing)
-        const int32_t Lv = min(vx->v_log2, max_level);
-        if (L < Lv) up = Lv - L;
-      }
-      if ((L < max_level) & ((((s.ni ^ ni) | (s.nj ^ nj)) >> up) != 0)) {
-        ni >>= up;
-        nj >>= up;
-        nL = L + up;
+      if ((L < max_level) & ((((s.ni ^ ni) | (s.nj ^ nj)) >> 1) != 0)) {
+        ni >>= 1;
+        nj >>= 1;
+        nL = L + 1;
       }
     }
     s.ni = ni;
@@ -720,8 +617,9 @@ __device__ __forceinline__ int32_t walk_steps(const tci_map& m, const lvl_t* lv,
 // keys alone, so the K columns ahead are loaded together first (indices
 // clamped into the map, so every load is valid) and then tested in order
 // from registers, and the walk waits on one round of loads instead of one
-// per cell.  Results and state as walk_steps<kSeg = true, kOcc = false,
-// kCap = true, kDir> with max_level 0: l0 is the cells' level record.
+// per cell.  Results and state as walk_steps<true, kDir> with
+// max_level 0 and a stop (kSegEnd) once the cell lies outside the lines
+// [seg_lo, seg_hi] of axis seg_axis (0 x, 1 y): l0 is the cells' level record.
 template <int kDir, int K>
 __device__ __forceinline__ int32_t walk_flat(const tci_map& m, const lvl_t l0, const ray_t& r,
                                              const walk_idx_t& k, walk_t& s, uint32_t& col,
