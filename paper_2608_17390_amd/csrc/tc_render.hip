@@ -167,13 +167,15 @@ __device__ __forceinline__ void render_body(
                  word, depth);
 }
 
-// The three one-thread-per-pixel kernels, each with and without read
-// counting.  The hierarchical one is asked for at least 7 waves per SIMD (at
-// most 72 VGPRs): 8 (64 VGPRs) spills in the walk loop and 6 (80 VGPRs, no
-// spill) hides less of its latency; 64 mixed views and 8 shadow passes take
-// 3.82 ms with 7, 3.91 with 8 and 4.04 with 6.
+// The one-thread-per-pixel kernels, each with and without read counting.
+// The hierarchical one runs 8 waves per SIMD (64 VGPRs, which its walk fits
+// without spilling vector registers): 64 mixed views and 8 shadow passes take
+// 3.56 ms with 8, 3.64 with 7 and 3.90 with 6, twelve 1280x800 views 335, 338
+// and 355 us.  A call whose tables come in the kernel's arguments has few
+// views and ends with its longest walks, which the 28 scalar registers that
+// 8 waves spill make longer (a 320x240 view 34.3 against 33.2 us): 7 there.
 template <bool kCount, bool kBoost>
-__global__ __launch_bounds__(64 * kPackets) __attribute__((amdgpu_waves_per_eu(7, 8)))
+__global__ __launch_bounds__(64 * kPackets) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void render_hier_kernel(tci_map m, const tci_view* __restrict__ views, int32_t nviews,
                         const int64_t* __restrict__ pkt_prefix, int64_t npkt, void* out,
                         tci_render_opts o) {
@@ -298,7 +300,7 @@ __device__ __forceinline__ void split_runs(const tci_map& m, const lvl_t* lv,
       } else {
         const float t = ((float)(b0 + (fwd ? 0 : 1) - oc) - (ax ? f.fx : f.fy)) * (ax ? f.rx : f.ry);
         const float p = fmaf(t, ax ? f.dy : f.dx, ax ? f.fy : f.fx);
-        int32_t c = (int32_t)floorf(p) + (ax ? f.cy : f.cx);
+        int32_t c = floor_int(p) + (ax ? f.cy : f.cx);
         if (__builtin_expect(!skim_sure(p), 0)) {
           ray_t r2 = r;
           walk_idx_t k;
@@ -312,20 +314,19 @@ __device__ __forceinline__ void split_runs(const tci_map& m, const lvl_t* lv,
         s.zin = fmaf(t, f.dz, r.Dz < 0 ? f.zhi : f.zlo);
       }
     }
-    int32_t it = 0, reads = 0;
+    int32_t reads = 0;
     uint32_t col = 0;
     float ze = 0.0f;
-    for (;;) {
+    for (int32_t round = 0;; ++round) {
       const uint64_t hit = __ballot(st == kHitCell) & group;
       if (st == kWalking && hit && lane > __ffsll((unsigned long long)hit) - 1) st = kSegEnd;
       if (!__ballot(st == kWalking)) break;
       if (st != kWalking) continue;
-      const int32_t stop = it + 16;
       if (r.Dz < 0)
-        st = skim_steps<1, kMinMax, true>(m, lv, f, s, Lmax, stop, it, col, ze, reads,
+        st = skim_steps<1, kMinMax, true>(m, lv, f, s, Lmax, 16, col, ze, reads,
                                           o.count != nullptr, ray, skim_test{}, ax, b1);
       else
-        st = skim_steps<2, kMinMax, true>(m, lv, f, s, Lmax, stop, it, col, ze, reads,
+        st = skim_steps<2, kMinMax, true>(m, lv, f, s, Lmax, 16, col, ze, reads,
                                           o.count != nullptr, ray, skim_test{}, ax, b1);
       if (st == kHitCell && !skim_sure_hit(f, s, col, ze, m.W, oz, word, depth)) {
         const skim_cell c = skim_exact_cell(ray(), s.x, s.y, col, m.W);
@@ -334,11 +335,10 @@ __device__ __forceinline__ void split_runs(const tci_map& m, const lvl_t* lv,
           depth = __uint_as_float(c.depth);
         } else {
           skim_step_whole(f, s, ray());
-          ++it;
           st = kWalking;
         }
       }
-      if (st == kWalking && it > kIterCap) {   // (never expected)
+      if (st == kWalking && round > kIterCap) {   // (never expected)
         st = kHitCell;
         word = kStuck;
         depth = __builtin_nanf("");

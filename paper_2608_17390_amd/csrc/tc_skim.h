@@ -78,9 +78,8 @@ __device__ __forceinline__ void skim_init(const ray_t& r, skim_ray& f) {
 // On which side of every line is q surely?  False if a line is too close.
 __device__ __forceinline__ bool skim_sure(float q) {
   const float fr = __builtin_amdgcn_fractf(q);
-  return fabsf(fr - 0.5f) < 0.5f - fmaf(fabsf(q), 0x1p-21f, 0x1p-20f);
+  return fabsf(fr - 0.5f) < fmaf(fabsf(q), -0x1p-21f, 0.5f - 0x1p-20f);
 }
-
 // Start at parameter t (in cells per direction unit; no solid lies on the
 // ray before it): in the ray's cell at t, on level 0, or at a slightly
 // earlier t if that cell is not sure, or at the origin on level L0.
@@ -93,8 +92,8 @@ __device__ __forceinline__ void skim_start(const skim_ray& f, float t, int32_t L
   }
   const bool at = (t > 0.0f) & skim_sure(qx) & skim_sure(qy);
   t = at ? t : 0.0f;
-  s.x = f.cx + (at ? (int32_t)floorf(qx) : 0);
-  s.y = f.cy + (at ? (int32_t)floorf(qy) : 0);
+  s.x = f.cx + (at ? floor_int(qx) : 0);
+  s.y = f.cy + (at ? floor_int(qy) : 0);
   s.L = at ? 0 : L0;
   s.zin = fmaf(t, f.dz, f.dz < 0.0f ? f.zhi : f.zlo);
 }
@@ -236,8 +235,7 @@ __device__ __forceinline__ void load_voxel_levels(const tci_voxels& vx, uint4* r
 }
 
 // Walk until a cell that may hold the hit (kHitCell, its column in col), a
-// certain miss (kMissed), or step number `budget` (kWalking); `it` counts the
-// steps, over several calls.  ze is the height at which the ray leaves that
+// certain miss (kMissed), or `budget` steps (kWalking).  ze is the height at which the ray leaves that
 // cell, moved by the margin to the other side than zin.  ray() gives the ray again for a step that is taken in whole
 // numbers, so that no register holds its integers through the walk.
 // kDir: 1 Dz < 0, 2 otherwise.
@@ -261,15 +259,15 @@ struct skim_test {
 template <int kDir, int kTest = kMinMax, bool kSeg = false, class RayFn>
 __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
                                               const skim_ray& f, skim_t& s, int32_t max_level,
-                                              int32_t budget, int32_t& it, uint32_t& col,
-                                              float& ze_out, int32_t& reads, bool count,
-                                              RayFn ray, const skim_test& t = skim_test{},
+                                              int32_t budget, uint32_t& col, float& ze_out,
+                                              int32_t& reads, bool count, RayFn ray,
+                                              const skim_test& t = skim_test{},
                                               bool seg_x = false, int32_t seg_end = 0) {
   const bool desc = kDir == 1;
   const bool fx = f.dx >= 0.0f, fy = f.dy >= 0.0f;
   const int32_t nx1 = fx ? 1 : 0, ny1 = fy ? 1 : 0;
   const float m2 = f.zhi - f.zlo;
-  for (; it < budget; ++it) {
+  for (int32_t it = 0; it < budget; ++it) {
     if constexpr (kSeg) {
       const int32_t c = seg_x ? s.x : s.y;
       if ((seg_x ? fx : fy) ? c >= seg_end : c <= seg_end) return kSegEnd;
@@ -282,7 +280,7 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
     const bool node = kTest != kVoxels || L == 0;   // tested against its word
     if (count) reads += (inmap & node) ? 1 : 0;
     const uint32_t ci = (uint32_t)clamp0(ni, w1), cj = (uint32_t)clamp0(nj, h1);
-    const uint32_t at = ((umul24(cj >> 3, lq.w) + (ci >> 3)) << 6) + ((cj & 7) << 3) + (ci & 7);
+    const uint32_t at = tiled_at(ci, cj, lq.w);
     const uint32_t v = map_word(m.base, lq.x + at);
     // times of the crossings through the far faces
     const int32_t gx = (ni + nx1) << L, gy = (nj + ny1) << L;
@@ -331,7 +329,7 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
       }
       if (!desc && ze > 255.0f + m2) return kMissed;
       const float q = fmaf(te, ex ? f.dy : f.dx, ex ? f.fy : f.fx);
-      const int32_t o = (int32_t)floorf(q) + (ex ? f.cy : f.cx);
+      const int32_t o = floor_int(q) + (ex ? f.cy : f.cx);
       int32_t x = ex ? gx + nx1 - 1 : o, y = ex ? o : gy + ny1 - 1;
       float zn = desc ? ze + m2 : ze - m2;
       if (__builtin_expect(!skim_sure(q), 0)) {
@@ -361,9 +359,13 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
 // in whole units, over the direction's component.  False: not settled (the
 // cell is then tested in whole numbers).  oz() gives the origin's height.
 template <class OzFn>
-__device__ __forceinline__ bool skim_sure_hit(const skim_ray& f, const skim_t& s, uint32_t v,
+__device__ __forceinline__ bool skim_sure_hit(const skim_ray& fr, const skim_t& s, uint32_t v,
                                               float ze, int32_t W, OzFn oz, uint32_t& word,
                                               float& depth) {
+  // (what depends on the ray alone is not to be computed ahead of the walk
+  // and held through it)
+  skim_ray f = fr;
+  asm volatile("" : "+v"(f.dx), "+v"(f.dy), "+v"(f.dz), "+v"(f.zlo));
   const bool down = f.dz < 0.0f;
   const float m2 = f.zhi - f.zlo, md = down ? m2 : 0.0f, mu = m2 - md;
   const float zil = s.zin - md, zih = s.zin + mu, zel = ze - mu, zeh = ze + md;
@@ -395,10 +397,7 @@ __device__ __forceinline__ bool skim_sure_hit(const skim_ray& f, const skim_t& s
                              : (down ? kTop : kUnder);
   const bool slab = entry ? !in_floor : (above | !down);
   word = (uint32_t)(s.y * W + s.x) | ((uint32_t)face << 27) | (slab ? 1u << 30 : 0u);
-  // (the length is not to be computed ahead of the walk and held through it)
-  float Dx = f.dx;
-  asm volatile("" : "+v"(Dx));
-  depth = hit_depth(fma((double)P, 65536.0, -(double)O), fabs((double)D), Dx, f.dy, f.dz);
+  depth = hit_depth(fma((double)P, 65536.0, -(double)O), fabs((double)D), f.dx, f.dy, f.dz);
   return true;
 }
 
@@ -413,7 +412,8 @@ __device__ __forceinline__ void skim_step_whole(const skim_ray& f, skim_t& s, co
 }
 
 // The whole walk: its state (kHitCell with the record in word and depth,
-// kMissed, or kWalking when the budget ran out).  With kBoost a wave raises
+// kMissed, or kWalking when the budget ran out; a ray that passes a cell
+// within the margin of its solid starts the budget anew).  With kBoost a wave raises
 // its issue priority after boost, 2 boost and 4 boost steps (an instance of
 // its own: the stops cost the walk 1.4 %).
 template <bool kBoost, int kTest, class RayFn, class OzFn>
@@ -422,22 +422,22 @@ __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
                                              int32_t budget, int32_t boost, int32_t& reads,
                                              bool count, RayFn ray, OzFn oz, uint32_t& word,
                                              float& depth, const skim_test& t) {
-  int32_t it = 0;
   uint32_t col = 0;
   float ze = 0.0f;
   const bool down = f.dz < 0.0f;
-  int32_t stop = kBoost && boost > 0 ? min(boost, budget) : budget;
+  int32_t raised = kBoost && boost > 0 ? 0 : 3;   // priority steps taken
   for (;;) {
+    const int32_t stop = !kBoost || raised == 3 ? budget : raised == 2 ? 2 * boost : boost;
     int32_t st;
     if (down)
-      st = skim_steps<1, kTest>(m, lv, f, s, max_level, stop, it, col, ze, reads, count, ray, t);
+      st = skim_steps<1, kTest>(m, lv, f, s, max_level, stop, col, ze, reads, count, ray, t);
     else
-      st = skim_steps<2, kTest>(m, lv, f, s, max_level, stop, it, col, ze, reads, count, ray, t);
-    if (kBoost && stop < budget && st == kWalking) {
-      if (stop == boost) __builtin_amdgcn_s_setprio(1);
-      else if (stop == 2 * boost) __builtin_amdgcn_s_setprio(2);
+      st = skim_steps<2, kTest>(m, lv, f, s, max_level, stop, col, ze, reads, count, ray, t);
+    if (kBoost && raised < 3 && st == kWalking) {
+      ++raised;
+      if (raised == 1) __builtin_amdgcn_s_setprio(1);
+      else if (raised == 2) __builtin_amdgcn_s_setprio(2);
       else __builtin_amdgcn_s_setprio(3);
-      stop = stop < 4 * boost ? min(2 * stop, budget) : budget;
       continue;
     }
     if (st != kHitCell) return st;
@@ -450,7 +450,6 @@ __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
     }
     // within the margin of solid, but not in it: on to the next cell
     skim_step_whole(f, s, ray());
-    ++it;
   }
 }
 
@@ -506,7 +505,7 @@ __device__ __forceinline__ bool skim_blocked(const tci_map& m, const lvl_t* lv, 
     s.x = x;
     s.y = y;
     if (__builtin_expect(skim_sure(p), 1)) {
-      const int32_t o = (int32_t)floorf(p);
+      const int32_t o = floor_int(p);
       s.x += ex ? (fx ? 1 : -1) : o;
       s.y += ex ? o : (fy ? 1 : -1);
       s.zin = desc ? zh : zl;
@@ -514,12 +513,11 @@ __device__ __forceinline__ bool skim_blocked(const tci_map& m, const lvl_t* lv, 
       skim_step_whole(f, s, q);
     }
   }
-  int32_t it = 0;
   for (;;) {
     uint32_t v = 0;
     float ze = 0.0f;
-    const int32_t st = skim_steps<kDir>(m, lv, f, s, max_level, kIterCap + 1, it, v, ze, reads,
-                                        kCount, [&]() { return q; });
+    const int32_t st = skim_steps<kDir>(m, lv, f, s, max_level, kIterCap + 1, v, ze, reads, kCount,
+                                        [&]() { return q; });
     if (st != kHitCell) return st != kMissed;
     // surely in solid, also with the heights moved by the margin the other
     // way; or else tested in whole numbers
@@ -528,7 +526,6 @@ __device__ __forceinline__ bool skim_blocked(const tci_map& m, const lvl_t* lv, 
     if (__builtin_expect((lo <= F) | (((v & 0xFF00) != 0) & (lo <= T) & (hi >= B)), 1)) return true;
     if (skim_exact_cell(q, s.x, s.y, v, m.W).hit) return true;
     skim_step_whole(f, s, q);
-    ++it;
   }
 }
 

@@ -188,6 +188,20 @@ __device__ __forceinline__ int64_t rfl64(int64_t x) {
 __device__ __forceinline__ uint32_t map_word(const uint32_t* base, uint32_t idx) {
   return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(base) + (idx << 2));
 }
+// Word of element (i, j) in a tiled level of `tiles` tiles per row.
+__device__ __forceinline__ uint32_t tiled_at(uint32_t i, uint32_t j, uint32_t tiles) {
+  uint32_t t;
+  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(t) : "v"(j >> 3), "v"(tiles), "v"(i >> 3));
+  return (t << 6) + (((j & 7) << 3) + (i & 7));
+}
+
+// floor(q) as an integer, in one instruction.
+__device__ __forceinline__ int32_t floor_int(float q) {
+  int32_t r;
+  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(q));
+  return r;
+}
+
 // a << L for an unsigned 32-bit a as a 64-bit value
 __device__ __forceinline__ int64_t ushl(uint32_t a, int32_t L) {
   return (int64_t)((uint64_t)a << L);
@@ -238,9 +252,20 @@ __device__ __forceinline__ void packet_ray(const tci_view& v, int32_t tx, int32_
   };
   constexpr int kN = kDir ? 6 : 3;
   if (v.small_steps) {
+    // (a pinhole view's origins are one point)
+    const bool pin = (v.opx[0] | v.opx[1] | v.opx[2] | v.opy[0] | v.opy[1] | v.opy[2]) == 0;
+    if (pin) {
+      for (int c = 0; c < 3; ++c) o[c] = v.o0[c];
+    } else {
 #pragma unroll
-    for (int c = 0; c < kN; ++c) {
-      const int32_t b = base(c < 3 ? v.o0[c] : v.d0[c - 3], step(c), stepy(c));
+      for (int c = 0; c < 3; ++c) {
+        const int32_t b = base(v.o0[c], step(c), stepy(c));
+        o[c] = __mul24(ly, 2 * stepy(c)) + (__mul24(lx, 2 * step(c)) + b);
+      }
+    }
+#pragma unroll
+    for (int c = 3; c < kN; ++c) {
+      const int32_t b = base(v.d0[c - 3], step(c), stepy(c));
       o[c] = __mul24(ly, 2 * stepy(c)) + (__mul24(lx, 2 * step(c)) + b);
     }
   } else {
