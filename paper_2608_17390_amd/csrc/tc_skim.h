@@ -341,7 +341,12 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
       // go up one level when the step entered a new parent node
       int32_t up = 1;
       if constexpr (kTest == kVoxels) up = max(min(t.vx->v_log2, max_level) - L, 1);
-      s.L = L + (((L < max_level) & (((uint32_t)((s.x ^ x) | (s.y ^ y)) >> (L + up - 1)) > 1u)) ? up : 0);
+      // (over voxels only with a new parent of that: their columns are mostly
+      // occupied near the terrain, and a climb that must descend again costs
+      // two steps; two cave views 164 -> 143, 256 -> 237, 253 -> 228 us, where
+      // the same rule made the pyramid's 64 mixed views 4 % slower)
+      const int32_t later = kTest == kVoxels ? 1 : 0;
+      s.L = L + (((L < max_level) & (((uint32_t)((s.x ^ x) | (s.y ^ y)) >> (L + up - 1 + later)) > 1u)) ? up : 0);
       s.x = x;
       s.y = y;
       s.zin = zn;
