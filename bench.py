@@ -21,7 +21,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # the sources of the headline traversal kernels (the committed profiles
 # record their hash)
 RENDER_SRCS = [os.path.join(ROOT, "paper_2608_17390_amd", "csrc", f)
-               for f in ("tc_walk.h", "tc_beam.h", "tc_packet.h", "tc_render.hip")]
+               for f in ("tc_walk.h", "tc_skim.h", "tc_beam.h", "tc_packet.h", "tc_render.hip")]
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
@@ -674,7 +674,7 @@ def main():
                      "traffic": traffic,
                      "traffic_gb_per_s": (traffic / (kavg * 1e-3) / 1e9) if traffic else None,
                      # VALU issue against the ALU roof (one wave64 VALU instruction per
-                     # SIMD every 2 cycles: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz):
+                     # SIMD every 2 cycles, the fastest kind: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz):
                      # SQ_INSTS_VALU over 1024 SIMDs x GRBM_GUI_ACTIVE per XCD x 0.5
                      "valu_issue_frac": profile_value(RENDER_SRCS, "render_c2_counters",
                                                       "valu_issue_frac"),
@@ -686,11 +686,11 @@ def main():
                      # (SQ_BUSY_CYCLES over 32 engines x GRBM_GUI_ACTIVE per XCD)
                      "sq_busy_frac": profile_value(RENDER_SRCS, "render_c2_counters",
                                                    "sq_busy_frac"),
-                     # the counters' verdict: neither HBM (measured traffic a fifth of the
-                     # algorithmic bytes, far below peak) nor VALU issue binds; each walk
-                     # step waits on the load of the step before, and the launch's tail
-                     # (its longest packets) leaves engines idle
-                     "binding_roof": "load_latency",
+                     # the counters' verdict: HBM moves a fifth of the algorithmic bytes, far
+                     # below peak; a VALU instruction of the walk's mix takes 3.1 to 3.4 cycles
+                     # of its SIMD, so issue binds while the launch is full (four fifths of
+                     # the time), and its longest walks in the rest
+                     "binding_roof": "valu_issue",
                      "kernel": KERNEL_NAMES[args.mode],
                      "alg_bytes_per_launch": alg_bytes,
                      "kernel_ms_avg": kavg,

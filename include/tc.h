@@ -319,9 +319,9 @@ tc_status tc_shade_views(tc_context *ctx, const tc_view *views, int32_t n,
                                     window levels of the min/max pyramid
                                     (one entry per box), at most this many
                                     times (Section 3.2's skip of empty space,
-                                    for a bundle); each ray then walks exactly
-                                    from the last cell line it enters before
-                                    t, so results are unchanged (0: rays start
+                                    for a bundle); each ray then walks from
+                                    the cell it is in at t, so results are
+                                    unchanged (0: rays start
                                     at the eye; 0..64, default 6) */
 /* Render mode 3 is the paper's sampled ray march (Section 3.1, RAYMARCH),
  * not an exact cast.  Per pixel the segment from the eye ends at the far

@@ -98,7 +98,7 @@ __device__ __forceinline__ void skim_start(const skim_ray& f, float t, int32_t L
   s.zin = fmaf(t, f.dz, f.dz < 0.0f ? f.zhi : f.zlo);
 }
 
-// A ray's integers, as the out-of-line steps take them.
+// A ray's integers, as the whole-number steps take them.
 struct skim_int {
   int32_t Ox, Oy, Oz, Dx, Dy, Dz;
 };
@@ -117,8 +117,8 @@ __device__ __forceinline__ ray_t skim_whole(const skim_int& q) {
 }
 
 // The step out of node (ni, nj) of level L in whole numbers: the cell it
-// enters, and whether it leaves through an x face.  Rare, so it is called
-// rather than inlined: its 64-bit values would raise the walk's registers.
+// enters, and whether it leaves through an x face.  Rare, but inlined: as a
+// call it spilled the walk's registers around it.
 struct skim_next {
   int32_t x, y, ex;
 };
@@ -141,7 +141,7 @@ __device__ __forceinline__ skim_next skim_exact_step(skim_int q, int32_t ni, int
 // Does the ray stop in cell (x, y) of its walk (packed column v)?  Then its
 // hit record (word, and depth's bits).  The crossing it enters the cell
 // through is the later of the cell's near x and y crossings (y on a tie,
-// since x steps first), if any.  Called, as skim_exact_step.
+// since x steps first), if any.  Inlined, as skim_exact_step.
 struct skim_cell {
   int32_t hit;
   uint32_t word, depth;
