@@ -460,6 +460,8 @@ tc_status tc_load_columns(tc_context* ctx, int32_t W, int32_t H,
     if (st) return st;
     hipStream_t s = (hipStream_t)hip_stream;
 
+    // (before the device's memory: it may throw)
+    std::vector<uint8_t> packed(row_stride != (size_t)W ? (size_t)W * H : 0);
     size_t words = 0;
     tci_map d = tci::layout_map(W, H, &words);
     uint32_t* map = nullptr;
@@ -475,11 +477,9 @@ tc_status tc_load_columns(tc_context* ctx, int32_t W, int32_t H,
     // each plane as one copy (a 2D copy of pageable memory runs row by row,
     // 149 ms for a plane of 2048 x 16384 against 1.3 ms); rows with gaps are
     // packed first
-    std::vector<uint8_t> packed;
     for (int k = 0; k < 3 && e == hipSuccess; ++k) {
       const uint8_t* rows = src[k];
-      if (row_stride != (size_t)W) {
-        packed.resize((size_t)W * H);
+      if (!packed.empty()) {
         for (int32_t y = 0; y < H; ++y)
           std::memcpy(packed.data() + (size_t)y * W, rows + (size_t)y * row_stride, W);
         rows = packed.data();
