@@ -48,8 +48,8 @@ constexpr int32_t kBeamStop = 4;
 // all inside the window of the first (tci_map.wl), so one window entry
 // bounds its solid: one load, counted in `reads`.  Every test is evaluated
 // and the answer combined without branches (lanes test different boxes, so
-// early returns would diverge): the load uses an index clamped into the
-// level, and the answer is the first of these that applies: no claim for a
+// early returns would diverge): the load is checked by its buffer's range,
+// and the answer is the first of these that applies: no claim for a
 // box with a NaN bound (never formed from valid views); clear above every
 // height; no claim for a huge box or one wider than the top level's nodes;
 // clear beside the map; else the window's test.  A box that starts before
@@ -74,9 +74,8 @@ __device__ __forceinline__ bool beam_box_solid(const tci_map& m, const lvl_t* lv
   const int32_t x0 = node(lox), y0 = node(loy);
   const lvl_t l = lv[L];
   const bool beside = (hix < 0.0f) | (hiy < 0.0f) | (x0 > l.w1) | (y0 > l.h1);
-  // index clamped into the level, so every lane's load is valid
-  const uint32_t i = (uint32_t)clamp0(x0, l.w1), j = (uint32_t)clamp0(y0, l.h1);
-  const uint32_t w = map_word(m.base, woff[L] + tiled_at(i, j, (uint32_t)l.tiles_x));
+  const uint32_t i = (uint32_t)max(x0, 0), j = (uint32_t)max(y0, 0);
+  const uint32_t w = buffer_word(map_buffer(m), woff[L] + tiled_at(i, j, (uint32_t)l.tiles_x));
   const bool test = !bad & !above & !huge & !wide & !beside;
   reads += test ? 1 : 0;
   // a window without a slab has smin = 255 > smax = 0, which fails the

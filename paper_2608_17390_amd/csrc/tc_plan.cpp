@@ -142,6 +142,7 @@ tci_map layout_map(int32_t W, int32_t H, size_t* words_out) {
     words += (size_t)k.tiles_x * ((k.h + 7) >> 3) * 64;
   }
   *words_out = words;
+  d.bytes = (uint32_t)(words * 4);
   return d;
 }
 

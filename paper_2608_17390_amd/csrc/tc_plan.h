@@ -48,6 +48,7 @@ struct tci_map {
   tci_level wl[TCI_MAX_LEVELS];   // window levels 0..top (off in words)
   int32_t W, H;
   int32_t top;                    // highest stored level (0 if none)
+  uint32_t bytes;                 // of the allocation (a buffer descriptor's range)
 };
 
 // The voxel occupancy pyramid of the voxel-accelerated march (Section 3.2):

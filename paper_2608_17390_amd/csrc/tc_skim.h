@@ -267,6 +267,7 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
   const bool fx = f.dx >= 0.0f, fy = f.dy >= 0.0f;
   const int32_t nx1 = fx ? 1 : 0, ny1 = fy ? 1 : 0;
   const float m2 = f.zhi - f.zlo;
+  const __amdgpu_buffer_rsrc_t buf = map_buffer(m);
   for (int32_t it = 0; it < budget; ++it) {
     if constexpr (kSeg) {
       const int32_t c = seg_x ? s.x : s.y;
@@ -279,9 +280,8 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
     const bool inmap = ((uint32_t)ni <= (uint32_t)w1) & ((uint32_t)nj <= (uint32_t)h1);
     const bool node = kTest != kVoxels || L == 0;   // tested against its word
     if (count) reads += (inmap & node) ? 1 : 0;
-    const uint32_t ci = (uint32_t)clamp0(ni, w1), cj = (uint32_t)clamp0(nj, h1);
-    const uint32_t at = tiled_at(ci, cj, lq.w);
-    const uint32_t v = map_word(m.base, lq.x + at);
+    const uint32_t at = tiled_at((uint32_t)ni, (uint32_t)nj, lq.w);
+    const uint32_t v = buffer_word(buf, lq.x + at);
     // times of the crossings through the far faces
     const int32_t gx = (ni + nx1) << L, gy = (nj + ny1) << L;
     const float tx = ((float)(gx - f.cx) - f.fx) * f.rx;

@@ -188,6 +188,20 @@ __device__ __forceinline__ int64_t rfl64(int64_t x) {
 __device__ __forceinline__ uint32_t map_word(const uint32_t* base, uint32_t idx) {
   return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(base) + (idx << 2));
 }
+// The map as a buffer, whose loads the hardware checks against the
+// allocation's end (beyond it they give 0): the index of a lane outside the
+// map need not be clamped, as its word is not looked at.  Two clamps of 4
+// cycles less per walk step, and one scalar base less beside the descriptor:
+// a full-HD view of long walks 148.0 -> 143.8 us, shaded 1280x800 views 126.1
+// -> 122.2 and 86.0 -> 84.2; a batch of 80 M rays 3.56 ms either way (its
+// 8-wave kernel spills 12 scalars more).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t map_buffer(const tci_map& m) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(m.base), 0, (int32_t)m.bytes,
+                                           0x00027000);
+}
+__device__ __forceinline__ uint32_t buffer_word(__amdgpu_buffer_rsrc_t b, uint32_t idx) {
+  return __builtin_amdgcn_raw_buffer_load_b32(b, (int32_t)(idx << 2), 0, 0);
+}
 // Word of element (i, j) in a tiled level of `tiles` tiles per row.
 __device__ __forceinline__ uint32_t tiled_at(uint32_t i, uint32_t j, uint32_t tiles) {
   uint32_t t;
