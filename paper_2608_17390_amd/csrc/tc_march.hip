@@ -33,7 +33,9 @@
 // march); the tiled layout keeps a packet's samples in few 256-byte tiles.
 // Twelve 1280x800 views, 128 samples: 560 us without the start, 320 with it
 // and groups of 8, 300 with 4 (288 against 283 for 2 and 4 on the final
-// loads), 270 with 32-bit load offsets and the packet's scalar ray set-up.
+// loads), 270 with 32-bit load offsets and the packet's scalar ray set-up,
+// 250 with the cell as an integer (its in-map test is two unsigned compares
+// for four of floats) and loads through the map's buffer (no clamps).
 // Skipping runs of samples by a box test per ray as well was slower (316-332
 // against 300): the lanes of a wave part over which of them to test.
 // Two exits skip samples that cannot be solid: a point left of, right of,
@@ -120,16 +122,16 @@ __global__ __launch_bounds__(64 * kPackets) void march_kernel(
     if (t_end > 0.0f) {
       const float dt = t_end / (float)(steps + 1);
       const float Wf = (float)m.W, Hf = (float)m.H;
-      const float Wm1 = (float)(m.W - 1), Hm1 = (float)(m.H - 1);
       const tci_level l0 = m.lv[0];
-      // the column under a point, clamped into the map so every lane loads
-      // without a branch (the clamp leaves the cell of a point over the map
-      // unchanged)
-      auto cell_at = [&](float x, float y) {
-        const uint32_t i = (uint32_t)__builtin_amdgcn_fmed3f(x, 0.0f, Wm1);
-        const uint32_t j = (uint32_t)__builtin_amdgcn_fmed3f(y, 0.0f, Hm1);
-        return map_word(m.base, l0.off + ((umul24(j >> 3, (uint32_t)l0.tiles_x) + (i >> 3)) << 6) +
-                                             ((j & 7) << 3) + (i & 7));
+      const __amdgpu_buffer_rsrc_t buf = map_buffer(m);
+      // the cell under a point (a conversion saturates), whether it is in the
+      // map, and its column (anything beside the map: the buffer's range
+      // keeps the load valid)
+      auto in_map = [&](int32_t i, int32_t j) {
+        return ((uint32_t)i < (uint32_t)m.W) & ((uint32_t)j < (uint32_t)m.H);
+      };
+      auto cell_at = [&](int32_t i, int32_t j) {
+        return buffer_word(buf, l0.off + tiled_at((uint32_t)i, (uint32_t)j, (uint32_t)l0.tiles_x));
       };
       // no later sample can be solid
       auto gone = [&](float x, float y, float z) {
@@ -155,8 +157,9 @@ __global__ __launch_bounds__(64 * kPackets) void march_kernel(
           const float t = (float)(i0 + u) * dt;
           at(r, t, x, y, z);
           zs[u] = z;
-          in[u] = i0 + u <= steps && x >= 0.0f && x < Wf && y >= 0.0f && y < Hf;
-          col[u] = cell_at(x, y);
+          const int32_t i = floor_int(x), j = floor_int(y);
+          in[u] = (i0 + u <= steps) & in_map(i, j);
+          col[u] = cell_at(i, j);
         }
         int32_t found = 0, tested = 0;
 #pragma unroll
@@ -179,19 +182,20 @@ __global__ __launch_bounds__(64 * kPackets) void march_kernel(
         float ta = (float)(hit_i - 1) * dt, tb = (float)hit_i * dt;
         float x, y, z;
         at(r, tb, x, y, z);
-        int32_t cx = (int32_t)x, cy = (int32_t)y;
-        int32_t layer = solid(cell_at(x, y), z);
+        int32_t cx = floor_int(x), cy = floor_int(y);
+        int32_t layer = solid(cell_at(cx, cy), z);
         for (int32_t k = 0; k < o.march_bisect; ++k) {
           const float tm = (ta + tb) * 0.5f;
           at(r, tm, x, y, z);
-          const bool inm = x >= 0.0f && x < Wf && y >= 0.0f && y < Hf;
+          const int32_t i = floor_int(x), j = floor_int(y);
+          const bool inm = in_map(i, j);
           if (kCount) reads += inm;
-          const uint32_t c = cell_at(x, y);
+          const uint32_t c = cell_at(i, j);
           const int32_t s = inm ? solid(c, z) : 0;
           if (s) {
             tb = tm;
-            cx = (int32_t)x;
-            cy = (int32_t)y;
+            cx = i;
+            cy = j;
             layer = s;
           } else {
             ta = tm;
