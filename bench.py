@@ -687,7 +687,7 @@ def main():
                      "sq_busy_frac": profile_value(RENDER_SRCS, "render_c2_counters",
                                                    "sq_busy_frac"),
                      # the counters' verdict: HBM moves a fifth of the algorithmic bytes, far
-                     # below peak; a VALU instruction of the walk's mix takes 3.1 to 3.4 cycles
+                     # below peak; a VALU instruction of the walk's mix takes 3.0 to 3.2 cycles
                      # of its SIMD, so issue binds while the launch is full (four fifths of
                      # the time), and its longest walks in the rest
                      "binding_roof": "valu_issue",
