@@ -121,16 +121,11 @@ __device__ __forceinline__ void render_body(
       packet_ray(v, tx, ty, lane_now(), q);
       return skim_int{(int32_t)q.Ox, (int32_t)q.Oy, (int32_t)q.Oz, q.Dx, q.Dy, q.Dz};
     };
-    auto oz = [&]() {
-      ray_t q;
-      packet_ray<false>(v, tx, ty, lane_now(), q);
-      return (int32_t)q.Oz;
-    };
     int32_t reads = beam_reads, st;
     for (;;) {
       const int32_t budget = split ? o.split_budget : kIterCap + 1;
-      st = skim_walk<kBoost, kTest>(m, lv, f, s, Lmax, budget, boost, reads, kCount, ray, oz, word,
-                                    depth, skim_test{moff, vx, vrec});
+      st = skim_walk<kBoost, kTest>(m, lv, f, s, Lmax, budget, boost, reads, kCount, ray, word, depth,
+                                     skim_test{moff, vx, vrec});
       if (!split) break;
       split = false;
       // long walks go to the split pass, as many as the queue holds
@@ -286,7 +281,6 @@ __device__ __forceinline__ void split_runs(const tci_map& m, const lvl_t* lv,
     auto ray = [&]() {
       return skim_int{(int32_t)r.Ox, (int32_t)r.Oy, (int32_t)r.Oz, r.Dx, r.Dy, r.Dz};
     };
-    auto oz = [&]() { return (int32_t)r.Oz; };
     if (e < n && b0 != b1) {
       st = kWalking;
       // the cell the ray enters line b0 in (the origin's cell, if that is
@@ -296,7 +290,7 @@ __device__ __forceinline__ void split_runs(const tci_map& m, const lvl_t* lv,
       if ((b0 - oc) * dir <= 0) {
         s.x = f.cx;
         s.y = f.cy;
-        s.zin = r.Dz < 0 ? f.zhi : f.zlo;
+        s.zin = f.oz;
       } else {
         const float t = ((float)(b0 + (fwd ? 0 : 1) - oc) - (ax ? f.fx : f.fy)) * (ax ? f.rx : f.ry);
         const float p = fmaf(t, ax ? f.dy : f.dx, ax ? f.fy : f.fx);
@@ -311,7 +305,7 @@ __device__ __forceinline__ void split_runs(const tci_map& m, const lvl_t* lv,
         }
         s.x = ax ? b0 : c;
         s.y = ax ? c : b0;
-        s.zin = fmaf(t, f.dz, r.Dz < 0 ? f.zhi : f.zlo);
+        s.zin = skim_zin(f, t, r.Dz < 0);
       }
     }
     int32_t reads = 0;
@@ -328,7 +322,7 @@ __device__ __forceinline__ void split_runs(const tci_map& m, const lvl_t* lv,
       else
         st = skim_steps<2, kMinMax, true>(m, lv, f, s, Lmax, 16, col, ze, reads,
                                           o.count != nullptr, ray, skim_test{}, ax, b1);
-      if (st == kHitCell && !skim_sure_hit(f, s, col, ze, m.W, oz, word, depth)) {
+      if (st == kHitCell && !skim_sure_hit(f, s, col, ze, m.W, ray, word, depth)) {
         const skim_cell c = skim_exact_cell(ray(), s.x, s.y, col, m.W);
         if (c.hit) {
           word = c.word;

@@ -1,0 +1,98 @@
+"""How many nodes and cells a walk reads where single precision decides
+little: rays a unit above a plateau, shadow rays of a level light.  Each is counted against rays of the same kind that rounding
+leaves nothing open for, and every record is the oracle's.  A walk that goes
+through such a stretch cell by cell reads hundreds per ray more."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+tc = pytest.importorskip("paper_2608_17390_amd")
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+from test_gpu_parity import assert_parity, load  # noqa: E402
+from test_gpu_shade import assert_same  # noqa: E402
+from test_gpu_skim import S, ortho  # noqa: E402
+
+K = 1 << 22
+N = 600       # cells a ray runs along the plateau
+LEVELS = 10   # of a 640-cell map: a walk climbs them and comes down again
+
+
+@pytest.fixture()
+def ctx():
+    with tc.Context(0) as c:
+        c.tc_set_option(tc.TC_OPT_COUNT_READS, 1)
+        yield c
+
+
+def counted(ctx, F, B, T, views, what):
+    ctx.tc_read_counters()
+    out = tc.render(ctx, views)
+    torch.cuda.synchronize()
+    n = ctx.tc_read_counters()
+    wo, do = oracle.render(F, B, T, views)
+    assert_parity(*tc.split_hits(out), wo, do, what)
+    return n / wo.size
+
+
+def plateau(axis):
+    F = np.full((640, 640), 100, np.uint8)
+    F[:, 10 + N:] = 140
+    F = F if axis == 0 else np.ascontiguousarray(F.T)
+    return F, np.zeros_like(F), np.zeros_like(F)
+
+
+# rays 1, 20 and 40 units above the plateau, against rays 2,048 above it (a
+# 32nd of a cell: within the packet beam's margin, so both kinds begin alike)
+@pytest.mark.parametrize("axis,slope", [(0, 0), (0, 9), (1, 0), (1, -11)])
+@pytest.mark.parametrize("mode,budget,w", [(0, 0, 40), (0, 5, 8), (0, 5, 70), (4, 0, 40), (5, 0, 40)])
+def test_plateau(ctx, mode, budget, w, axis, slope):
+    F, B, T = plateau(axis)
+    ctx.tc_set_option(tc.TC_OPT_VOXEL_SHAPE, 4 | 2 << 8)
+    ctx.tc_set_option(tc.TC_OPT_RENDER_MODE, mode)
+    ctx.tc_set_option(tc.TC_OPT_SPLIT_BUDGET, budget)
+    load(ctx, F, B, T)
+    d = (K, slope * K // 100) if axis == 0 else (slope * K // 100, K)
+    o = (9 * S + 3, 200 * S + 77) if axis == 0 else (200 * S + 77, 9 * S + 3)
+    step = (0, S, 0) if axis == 0 else (S, 0, 0)
+
+    def view(dz):
+        return ortho(o + (100 * S + dz,), step, (0, 0, 0), d + (0,), w, 20)
+
+    got = {}
+    for dz in (2048, 1, 20, 40):
+        print(mode, budget, w, axis, slope, dz, flush=True)
+        got[dz] = counted(ctx, F, B, T, [view(dz)], "%d above" % dz)
+    # one more climb and descent, of two reads a level each at the most
+    for dz in (1, 20, 40):
+        runs = 1 if budget == 0 or w > 50 else 256   # (a run of its own per cell)
+        assert got[dz] <= got[2048] + 4 * LEVELS * min(runs, 64), got
+
+
+# a step at x = 4 and beyond it a plateau as high as the step, or one lower
+@pytest.mark.parametrize("light", [(K, 0, 0), (K, 1234567, 0), (K, -7, 5), (K, K // 3, 400)])
+def test_level_light(ctx, light):
+    pal = synth.default_palette()
+    got = {}
+    for far in (99, 100):
+        F = np.full((64, 640), 100, np.uint8)
+        F[:, 5:8] = 99
+        F[:, 8:] = far
+        Z = np.zeros_like(F)
+        load(ctx, F, Z, Z)
+        # straight down on the step's top, whose normal leans to the light
+        v = ortho((4 * S, 0, 200 * S), (S // 64, 0, 0), (0, S // 2, 0), (0, 0, -K), 32, 48)
+        hits = tc.render(ctx, [v])
+        rgba = torch.empty(32 * 48, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        ctx.tc_read_counters()
+        print(light, far, flush=True)
+        ctx.tc_shade_views([v], hits.data_ptr(), light, pal, rgba.data_ptr())
+        torch.cuda.synchronize()
+        got[far] = ctx.tc_read_counters() / (32 * 48)
+        assert_same(rgba.cpu().numpy().view(np.uint32), oracle.shade(F, Z, Z, [v], light, pal), str(light))
+    assert got[100] <= got[99] + 4 * LEVELS, got
