@@ -1,5 +1,6 @@
 """How many nodes and cells a walk reads where single precision decides
-little: rays a unit above a plateau, shadow rays of a level light.  Each is counted against rays of the same kind that rounding
+little: rays a unit above a plateau, shadow rays of a level light, rays along
+cell lines.  Each is counted against rays of the same kind that rounding
 leaves nothing open for, and every record is the oracle's.  A walk that goes
 through such a stretch cell by cell reads hundreds per ray more."""
 import numpy as np
@@ -96,3 +97,30 @@ def test_level_light(ctx, light):
         got[far] = ctx.tc_read_counters() / (32 * 48)
         assert_same(rgba.cpu().numpy().view(np.uint32), oracle.shade(F, Z, Z, [v], light, pal), str(light))
     assert got[100] <= got[99] + 4 * LEVELS, got
+
+
+# every ray on a cell line, against the same rays half a cell beside it, over
+# a map that is the same along the other axis: both begin in the cell where
+# the beam ends, and read the same
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("mode", [0, 4, 5])
+def test_cell_lines(ctx, mode, axis, sign):
+    prof = synth.make_map(640, 64, 5, dual=0.2, period=64)
+    F, B, T = (np.ascontiguousarray(np.repeat(p[:1], 640, 0)) for p in prof)
+    if axis == 1:
+        F, B, T = (np.ascontiguousarray(p.T) for p in (F, B, T))
+    ctx.tc_set_option(tc.TC_OPT_VOXEL_SHAPE, 4 | 2 << 8)
+    ctx.tc_set_option(tc.TC_OPT_RENDER_MODE, mode)
+    ctx.tc_set_option(tc.TC_OPT_SPLIT_BUDGET, 0)
+    load(ctx, F, B, T)
+    got = {}
+    for off in (S // 2, 0):
+        along, across = (-40 * S if sign > 0 else 680 * S) + 5, 100 * S + off
+        o = (along, across, 90 * S) if axis == 0 else (across, along, 90 * S)
+        d = (sign * K, 0, -K // 30) if axis == 0 else (0, sign * K, -K // 30)
+        step = (0, S // 2, 0) if axis == 0 else (S // 2, 0, 0)
+        print(mode, axis, sign, off, flush=True)
+        got[off] = counted(ctx, F, B, T, [ortho(o, step, (0, 0, S // 4), d, 64, 300)], "offset %d" % off)
+    # (the beam's boxes of the two lie half a cell apart)
+    assert abs(got[0] - got[S // 2]) <= 0.02 * got[S // 2], got
