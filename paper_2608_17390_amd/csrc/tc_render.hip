@@ -318,17 +318,17 @@ __device__ __forceinline__ void split_runs(const tci_map& m, const lvl_t* lv,
       if (st != kWalking) continue;
       if (r.Dz < 0)
         st = skim_steps<1, kMinMax, true>(m, lv, f, s, Lmax, 16, col, ze, reads,
-                                          o.count != nullptr, ray, skim_test{}, ax, b1);
+                                          o.count != nullptr, skim_test{}, ax, b1);
       else
         st = skim_steps<2, kMinMax, true>(m, lv, f, s, Lmax, 16, col, ze, reads,
-                                          o.count != nullptr, ray, skim_test{}, ax, b1);
+                                          o.count != nullptr, skim_test{}, ax, b1);
       if (st == kHitCell && !skim_sure_hit(f, s, col, ze, m.W, ray, word, depth)) {
         const skim_cell c = skim_exact_cell(ray(), s.x, s.y, col, m.W);
         if (c.hit) {
           word = c.word;
           depth = __uint_as_float(c.depth);
         } else {
-          skim_step_whole(f, s, ray());
+          skim_step(f, s);
           st = kWalking;
         }
       }

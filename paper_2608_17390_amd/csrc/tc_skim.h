@@ -24,8 +24,8 @@
 //     plus one rounding.  A q farther than that from a cell line has the
 //     right cell (and then the face it leaves through is right as well: were
 //     the other face crossed first, q would lie outside the node).  A q
-//     closer to a line than 2^-21 |q| + 2^-20 is left to `exact`, which
-//     takes the step in whole numbers (skim_exact_step);
+//     closer to a line than 2^-21 |q| + 2^-20 is decided by the exact order
+//     of the two crossings (corner_step);
 //   * a node is skipped only if the ray's heights over it, widened by a
 //     margin, meet no solid.  A height is off by what its time is, 2^-22 of
 //     the ray's rise or fall so far, so the margin is 2^-20 of that (and what
@@ -46,6 +46,7 @@
 // crossings' keys to descend.
 #pragma once
 
+#include "tc_corner.h"
 #include "tc_walk.h"
 
 namespace {
@@ -150,32 +151,11 @@ __device__ __forceinline__ ray_t skim_whole(const skim_int& q) {
   return r;
 }
 
-// The step out of node (ni, nj) of level L in whole numbers: the cell it
-// enters, and whether it leaves through an x face.  Rare, but inlined: as a
-// call it spilled the walk's registers around it.
-struct skim_next {
-  int32_t x, y, ex;
-};
-__device__ __forceinline__ skim_next skim_exact_step(skim_int q, int32_t ni, int32_t nj,
-                                                               int32_t L) {
-  ray_t r = skim_whole(q);
-  walk_idx_t k;
-  walk_t w;
-  walk_origin(r, k);
-  const bool fx = r.Dx > 0, fy = r.Dy > 0;
-  const int32_t ix = far_index(ni, L, fx ? 1 : 0, fx ? 1 : -1, k.offx);
-  const int32_t iy = far_index(nj, L, fy ? 1 : 0, fy ? 1 : -1, k.offy);
-  const bool ex = add_mul48(k.KX0, (uint32_t)ix, r.ay) <= add_mul48(k.KY0, (uint32_t)iy, r.ax);
-  const int32_t line = ex ? (fx ? (ni + 1) << L : (ni << L) - 1)
-                          : (fy ? (nj + 1) << L : (nj << L) - 1);
-  walk_at_line(r, k, w, ex ? 0 : 1, line);
-  return skim_next{w.ni, w.nj, ex ? 1 : 0};
-}
-
 // Does the ray stop in cell (x, y) of its walk (packed column v)?  Then its
 // hit record (word, and depth's bits).  The crossing it enters the cell
 // through is the later of the cell's near x and y crossings (y on a tie,
-// since x steps first), if any.  Inlined, as skim_exact_step.
+// since x steps first), if any.  Rare, but inlined: as a call it spilled the
+// walk's registers around it.
 struct skim_cell {
   int32_t hit;
   uint32_t word, depth;
@@ -270,8 +250,7 @@ __device__ __forceinline__ void load_voxel_levels(const tci_voxels& vx, uint4* r
 
 // Walk until a cell that may hold the hit (kHitCell, its column in col), a
 // certain miss (kMissed), or `budget` steps (kWalking).  ze is the height at which the ray leaves that
-// cell, moved by the margin to the other side than zin.  ray() gives the ray again for a step that is taken in whole
-// numbers, so that no register holds its integers through the walk.
+// cell, moved by the margin to the other side than zin.
 // kDir: 1 Dz < 0, 2 otherwise.
 // kTest: what a node above the cells is tested against.  kMinMax: its
 // min/max pyramid node.  kMasks: a node that only the slab test keeps, also
@@ -290,11 +269,11 @@ struct skim_test {
 };
 // With kSeg the walk also ends (kSegEnd) once it enters a cell at or beyond
 // line seg_end of axis seg_x (x or y), in the ray's direction.
-template <int kDir, int kTest = kMinMax, bool kSeg = false, class RayFn>
+template <int kDir, int kTest = kMinMax, bool kSeg = false>
 __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
                                               const skim_ray& f, skim_t& s, int32_t max_level,
                                               int32_t budget, uint32_t& col, float& ze_out,
-                                              int32_t& reads, bool count, RayFn ray,
+                                              int32_t& reads, bool count,
                                               const skim_test& t = skim_test{},
                                               bool seg_x = false, int32_t seg_end = 0) {
   const bool desc = kDir == 1;
@@ -368,7 +347,7 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
       const int32_t o = floor_int(q) + (ex ? f.cy : f.cx);
       int32_t x = ex ? gx + nx1 - 1 : o, y = ex ? o : gy + ny1 - 1;
       if (__builtin_expect(!skim_sure(q) & !gone, 0)) {
-        const skim_next n = skim_exact_step(ray(), ni, nj, L);
+        const skim_next n = corner_step(f.cx, f.cy, f.fx, f.fy, f.dx, f.dy, gx, gy, ex, q);
         x = n.x;
         y = n.y;
         zn = skim_zin(f, n.ex ? tx : ty, desc);
@@ -451,14 +430,20 @@ __device__ __forceinline__ bool skim_sure_hit(const skim_ray& fr, const skim_t& 
   return true;
 }
 
-// The step out of the current cell (level 0) in whole numbers.
-__device__ __forceinline__ void skim_step_whole(const skim_ray& f, skim_t& s, const skim_int& q) {
-  const skim_next n = skim_exact_step(q, s.x, s.y, 0);
-  const float t = n.ex ? ((float)(s.x + (f.dx >= 0.0f ? 1 : 0) - f.cx) - f.fx) * f.rx
-                       : ((float)(s.y + (f.dy >= 0.0f ? 1 : 0) - f.cy) - f.fy) * f.ry;
+// The step out of the current cell (level 0).
+__device__ __forceinline__ void skim_step(const skim_ray& f, skim_t& s) {
+  const bool fx = f.dx >= 0.0f, fy = f.dy >= 0.0f;
+  const int32_t gx = s.x + (fx ? 1 : 0), gy = s.y + (fy ? 1 : 0);
+  const float tx = ((float)(gx - f.cx) - f.fx) * f.rx, ty = ((float)(gy - f.cy) - f.fy) * f.ry;
+  const bool ex = tx <= ty;
+  const float q = fmaf(fminf(tx, ty), ex ? f.dy : f.dx, ex ? f.fy : f.fx);
+  const int32_t o = floor_int(q) + (ex ? f.cy : f.cx);
+  skim_next n{ex ? gx + (fx ? 0 : -1) : o, ex ? o : gy + (fy ? 0 : -1), ex ? 1 : 0};
+  if (__builtin_expect(!skim_sure(q), 0))
+    n = corner_step(f.cx, f.cy, f.fx, f.fy, f.dx, f.dy, gx, gy, ex, q);
   s.x = n.x;
   s.y = n.y;
-  s.zin = skim_zin(f, t, f.dzl < 0.0f);
+  s.zin = skim_zin(f, n.ex ? tx : ty, f.dzl < 0.0f);
 }
 
 // The whole walk: its state (kHitCell with the record in word and depth,
@@ -480,9 +465,9 @@ __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
     const int32_t stop = !kBoost || raised == 3 ? budget : raised == 2 ? 2 * boost : boost;
     int32_t st;
     if (down)
-      st = skim_steps<1, kTest>(m, lv, f, s, max_level, stop, col, ze, reads, count, ray, t);
+      st = skim_steps<1, kTest>(m, lv, f, s, max_level, stop, col, ze, reads, count, t);
     else
-      st = skim_steps<2, kTest>(m, lv, f, s, max_level, stop, col, ze, reads, count, ray, t);
+      st = skim_steps<2, kTest>(m, lv, f, s, max_level, stop, col, ze, reads, count, t);
     if (kBoost && raised < 3 && st == kWalking) {
       ++raised;
       if (raised == 1) __builtin_amdgcn_s_setprio(1);
@@ -499,7 +484,7 @@ __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
       return kHitCell;
     }
     // within the margin of solid, but not in it: on to the next cell
-    skim_step_whole(f, s, ray());
+    skim_step(f, s);
   }
 }
 
@@ -551,24 +536,15 @@ __device__ __forceinline__ bool skim_blocked(const tci_map& m, const lvl_t* lv, 
     const bool away = ((x < 0) & (f.dx <= 0.0f)) | ((x > l.w1) & fx) |
                       ((y < 0) & (f.dy <= 0.0f)) | ((y > l.h1) & fy);
     if (away) return false;
-    const float p = fmaf(te, ex ? f.dy : f.dx, ex ? f.fy : f.fx);
     s.L = 0;
     s.x = x;
     s.y = y;
-    if (__builtin_expect(skim_sure(p), 1)) {
-      const int32_t o = floor_int(p);
-      s.x += ex ? (fx ? 1 : -1) : o;
-      s.y += ex ? o : (fy ? 1 : -1);
-      s.zin = desc ? zh : zl;
-    } else {
-      skim_step_whole(f, s, q);
-    }
+    skim_step(f, s);
   }
   for (;;) {
     uint32_t v = 0;
     float ze = 0.0f;
-    const int32_t st = skim_steps<kDir>(m, lv, f, s, max_level, kIterCap + 1, v, ze, reads, kCount,
-                                        [&]() { return q; });
+    const int32_t st = skim_steps<kDir>(m, lv, f, s, max_level, kIterCap + 1, v, ze, reads, kCount);
     if (st != kHitCell) return st != kMissed;
     // surely in solid, also with the heights moved the other way; or else
     // tested in whole numbers
@@ -577,7 +553,7 @@ __device__ __forceinline__ bool skim_blocked(const tci_map& m, const lvl_t* lv, 
     const float F = (float)(v & 0xFF), B = (float)((v >> 8) & 0xFF), T = (float)((v >> 16) & 0xFF);
     if (__builtin_expect((lo <= F) | (((v & 0xFF00) != 0) & (lo <= T) & (hi >= B)), 1)) return true;
     if (skim_exact_cell(q, s.x, s.y, v, m.W).hit) return true;
-    skim_step_whole(f, s, q);
+    skim_step(f, s);
   }
 }
 

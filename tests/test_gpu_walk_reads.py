@@ -2,7 +2,8 @@
 little: rays a unit above a plateau, shadow rays of a level light, rays along
 cell lines.  Each is counted against rays of the same kind that rounding
 leaves nothing open for, and every record is the oracle's.  A walk that goes
-through such a stretch cell by cell reads hundreds per ray more."""
+through such a stretch cell by cell reads hundreds per ray more.  Rays through
+corners read no more; they are timed."""
 import numpy as np
 import pytest
 
@@ -124,3 +125,25 @@ def test_cell_lines(ctx, mode, axis, sign):
         got[off] = counted(ctx, F, B, T, [ortho(o, step, (0, 0, S // 4), d, 64, 300)], "offset %d" % off)
     # (the beam's boxes of the two lie half a cell apart)
     assert abs(got[0] - got[S // 2]) <= 0.02 * got[S // 2], got
+
+
+# rays that meet a corner at every crossing, against those that pass beside
+# them: the exact order of two crossings costs as much again as the step, not
+# several times as much (medians of the kernels' own times, in turn)
+@pytest.mark.parametrize("d", [(K, K), (-K, K), (K // 3, 3 * (K // 3))])
+def test_corner_time(ctx, d):
+    F, B, T = synth.make_map(1024, 1024, 6, dual=0.2, period=128)
+    ctx.tc_set_option(tc.TC_OPT_COUNT_READS, 0)
+    ctx.tc_set_option(tc.TC_OPT_KERNEL_TIMING, 1)
+    load(ctx, F, B, T)
+    out = torch.empty((1000 * 1000, 2), dtype=torch.int32, device="cuda")
+    ms = {0: [], 12345: []}
+    for _ in range(15):
+        for off in ms:
+            v = ortho((off if d[0] > 0 else 1024 * S - off, 0, 260 * S), (S // 2 * (1 if d[0] > 0 else -1), 0, 0),
+                      (0, S // 2, 0), d + (-K // 24,), 1000, 1000)
+            ctx.tc_render_views([v], out.data_ptr())
+            ms[off].append(sum(ctx.tc_read_kernel_times()))
+    on, beside = (np.median(ms[k][3:]) for k in (0, 12345))
+    print(d, on, beside, flush=True)
+    assert on <= 2.0 * beside, (on, beside)
