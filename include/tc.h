@@ -293,10 +293,10 @@ tc_status tc_shade_views(tc_context *ctx, const tc_view *views, int32_t n,
                                     path per wave in parallel (4 waves by
                                     default), each from the exact state the
                                     walk enters it with, or as many runs as
-                                    there are lanes for if the rays are many.
-                                    A launch whose packets all run at once
-                                    hands rays over after at most 48 steps
-                                    (0: no second pass; default 120) */
+                                    there are lanes for if the rays are many
+                                    (0: no second pass).  The default, 120,
+                                    is 48 in a launch whose packets all run
+                                    at once; another value is used as it is */
 #define TC_OPT_SPLIT_QUEUE 12    /* most rays the second pass takes per call;
                                     further long rays finish in the first
                                     pass (1..2^24, default 131072; every slot
@@ -393,7 +393,7 @@ void tc_frame_destroy(tc_frame *frame);
 /* ---- autotuning ----------------------------------------------------------- */
 /* Time tc_render_views on these views (reps timed calls per setting, median)
  * over a grid of the render knobs -- traversal mode, start level, packet
- * order, XCD grouping, split budget (0 or 120), and the persistent queue's
+ * order, XCD grouping, split budget (0 or 120, the default), and the persistent queue's
  * waves per CU, refill threshold and refill interval, then the packet beam
  * passes (0, 2, 4, 6 or 8) of the best one-thread-per-pixel setting, then the
  * packet shape (width 4, 8, 16 or 32), the split budget (96, 112, 128 or 160, when

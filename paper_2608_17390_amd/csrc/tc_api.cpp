@@ -257,19 +257,19 @@ int32_t render_counter_words(const tc_context* ctx, const ViewPlan& p) {
 
 namespace {
 
-// Steps before a ray goes to the split pass.  A launch whose packets all run
-// at once ends with its longest walk, and the split pass's waves have the
-// whole GPU after it: it hands its rays over after kSmallBudget steps at
-// most.  With more packets than that the SIMDs issue all the time, and the
-// budget stays the option's.  320x240 views: 12 + 4 us (render and pass)
+// Steps before a ray goes to the split pass: the option's, or where that is at
+// its default and the launch's packets all run at once (`waves` a SIMD, what
+// the kernel's registers allow) kSmallBudget.  Such a launch ends with its
+// longest walk, and the split pass's waves have the whole GPU after it; with
+// more packets the SIMDs issue all the time.  320x240 views: 12 + 4 us (render and pass)
 // with any budget where walks are short; where they are long 37 + 4, 24 + 8
 // and 19 + 19 us at 120, 48 and 32 steps.  Seven edits with a 640x480 view
 // each: 691, 619, 638 us in all at 120, 64 and 48, seven 320x240 views 239,
 // 239 and 221.  1920x1080 views: 127 + 22 us at 120, 101 + 98 at 48.
 constexpr int32_t kSmallBudget = 48;
-int32_t split_budget(const tc_context* ctx, const ViewPlan& p) {
-  const int64_t waves = (int64_t)ctx->num_cu * 4 * 7;   // the render's, at once
-  return p.npkt <= waves ? std::min(ctx->split_budget, kSmallBudget) : ctx->split_budget;
+int32_t split_budget(const tc_context* ctx, const ViewPlan& p, int32_t waves) {
+  return ctx->split_budget == kSplitBudget && p.npkt <= (int64_t)ctx->num_cu * 4 * waves
+             ? kSmallBudget : ctx->split_budget;
 }
 // Blocks of the split pass (4 / qwaves queued rays per block of 4 waves): at
 // most those that run at once (four waves a SIMD), which stride over the
@@ -297,7 +297,7 @@ hipError_t enqueue_render(tc_context* ctx, const tci_map& d, const char* dev,
     // the traversal and kev[2..3] the split pass)
     if (split_ran) *split_ran = false;
     if (p.qcap > 0) {
-      o.split_budget = split_budget(ctx, p);
+      o.split_budget = split_budget(ctx, p, 7);
       o.qcap = p.qcap;
       o.queue = queue;
       o.qcount = qctr;
@@ -338,7 +338,7 @@ hipError_t enqueue_render(tc_context* ctx, const tci_map& d, const char* dev,
   }
   if (p.qcap > 0) {
     uint64_t* counters = (uint64_t*)(dev + p.off_counter);
-    o.split_budget = split_budget(ctx, p);
+    o.split_budget = split_budget(ctx, p, 8);
     o.qcap = p.qcap;
     o.queue = queue ? queue : (uint4*)(dev + p.off_queue);
     o.qcount = (uint32_t*)(counters + 1);

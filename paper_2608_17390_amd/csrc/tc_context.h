@@ -22,6 +22,8 @@ constexpr size_t kSlotBytes = 256 << 10;
 // the level below the group: a node then combines at most 8 x 8 nodes of
 // that level, a window entry at most 8 x 8.
 constexpr int32_t kUpdateGroup = 3;
+// Default of TC_OPT_SPLIT_BUDGET.
+constexpr int32_t kSplitBudget = 120;
 
 // A pinned host buffer and a device buffer of the same size, reused across
 // calls, plus a device-only split queue (never uploaded, so it has no host
@@ -136,7 +138,7 @@ struct tc_context {
   int32_t tile_order = 2;
   int32_t packet_width = 8;
   int32_t boost = 0;
-  int32_t split_budget = 120;
+  int32_t split_budget = tci::kSplitBudget;
   int32_t beam_passes = 6;
   int32_t split_waves = 4;
   int32_t split_queue = 1 << 17;

@@ -147,3 +147,27 @@ def test_corner_time(ctx, d):
     on, beside = (np.median(ms[k][3:]) for k in (0, 12345))
     print(d, on, beside, flush=True)
     assert on <= 2.0 * beside, (on, beside)
+
+
+def rough(ctx):
+    F, B, T = synth.make_map(250, 310, 78, dual=0.3, period=64)
+    load(ctx, F, B, T)
+    v = [synth.perspective_view(synth.eye_above_floor(F, B, 33.5, 10.5), 12, 1, 160, 120)]
+    ctx.tc_set_option(tc.TC_OPT_BEAM_PASSES, 0)
+
+    def reads(budget):
+        ctx.tc_set_option(tc.TC_OPT_SPLIT_BUDGET, budget)
+        print(budget, flush=True)
+        return counted(ctx, F, B, T, v, "budget %d" % budget)
+    return reads
+
+
+# the runs of the split pass read more than the walk they take the place of,
+# so a walk that reaches them shows in the count
+def test_split_budget_is_the_one_set(ctx):
+    reads = rough(ctx)
+    never = reads(0)
+    assert reads(20) > never
+    assert reads(120) > never        # the default: fewer in a launch this small
+    for budget in (119, 121, 1 << 20):
+        assert reads(budget) == never   # no walk of this view is as long
