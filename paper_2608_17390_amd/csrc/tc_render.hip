@@ -121,13 +121,14 @@ __device__ __forceinline__ void render_body(
       packet_ray(v, tx, ty, lane_now(), q);
       return skim_int{(int32_t)q.Ox, (int32_t)q.Oy, (int32_t)q.Oz, q.Dx, q.Dy, q.Dz};
     };
-    int32_t reads = beam_reads, st;
+    int32_t reads = beam_reads, st, done = 0;
     for (;;) {
       const int32_t budget = split ? o.split_budget : kIterCap + 1;
-      st = skim_walk<kBoost, kTest>(m, lv, f, s, Lmax, budget, boost, reads, kCount, ray, word, depth,
-                                     skim_test{moff, vx, vrec});
+      st = skim_walk<kBoost, kTest>(m, lv, f, s, Lmax, budget, done, boost, reads, kCount, ray, word,
+                                     depth, skim_test{moff, vx, vrec});
       if (!split) break;
       split = false;
+      done = budget;
       // long walks go to the split pass, as many as the queue holds
       const uint64_t want = __ballot(st == kWalking);
       if (!want) break;

@@ -448,32 +448,35 @@ __device__ __forceinline__ void skim_step(const skim_ray& f, skim_t& s) {
 
 // The whole walk: its state (kHitCell with the record in word and depth,
 // kMissed, or kWalking when the budget ran out; a ray that passes a cell
-// within the margin of its solid starts the budget anew).  With kBoost a wave raises
-// its issue priority after boost, 2 boost and 4 boost steps (an instance of
-// its own: the stops cost the walk 1.4 %).
+// within the margin of its solid starts the budget anew).  With kBoost a wave
+// raises its issue priority after boost, 2 boost and 4 boost steps of its walk,
+// of which it has taken `done` before (an instance of its own: the stops cost
+// the walk 1.4 %).
 template <bool kBoost, int kTest, class RayFn>
 __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
                                              const skim_ray& f, skim_t& s, int32_t max_level,
-                                             int32_t budget, int32_t boost, int32_t& reads,
-                                             bool count, RayFn ray, uint32_t& word,
-                                             float& depth, const skim_test& t) {
+                                             int32_t budget, int32_t done, int32_t boost,
+                                             int32_t& reads, bool count, RayFn ray,
+                                             uint32_t& word, float& depth, const skim_test& t) {
   uint32_t col = 0;
   float ze = 0.0f;
   const bool down = f.dzl < 0.0f;
-  int32_t raised = kBoost && boost > 0 ? 0 : 3;   // priority steps taken
+  int32_t used = done;
+  const int32_t end = done + budget;
   for (;;) {
-    const int32_t stop = !kBoost || raised == 3 ? budget : raised == 2 ? 2 * boost : boost;
-    int32_t st;
+    int32_t stop = end - used, st;
+    if (kBoost && used < 4 * boost)
+      stop = min(stop, (used < boost ? boost : used < 2 * boost ? 2 * boost : 4 * boost) - used);
     if (down)
       st = skim_steps<1, kTest>(m, lv, f, s, max_level, stop, col, ze, reads, count, t);
     else
       st = skim_steps<2, kTest>(m, lv, f, s, max_level, stop, col, ze, reads, count, t);
-    if (kBoost && raised < 3 && st == kWalking) {
-      ++raised;
-      if (raised == 1) __builtin_amdgcn_s_setprio(1);
-      else if (raised == 2) __builtin_amdgcn_s_setprio(2);
-      else __builtin_amdgcn_s_setprio(3);
-      continue;
+    if (kBoost && st == kWalking) {
+      used += stop;
+      if (used == boost) __builtin_amdgcn_s_setprio(1);
+      else if (used == 2 * boost) __builtin_amdgcn_s_setprio(2);
+      else if (used == 4 * boost) __builtin_amdgcn_s_setprio(3);
+      if (used < end) continue;
     }
     if (st != kHitCell) return st;
     if (__builtin_expect(skim_sure_hit(f, s, col, ze, m.W, ray, word, depth), 1)) return kHitCell;

@@ -155,10 +155,11 @@ def rough(ctx):
     v = [synth.perspective_view(synth.eye_above_floor(F, B, 33.5, 10.5), 12, 1, 160, 120)]
     ctx.tc_set_option(tc.TC_OPT_BEAM_PASSES, 0)
 
-    def reads(budget):
+    def reads(budget, boost=0):
         ctx.tc_set_option(tc.TC_OPT_SPLIT_BUDGET, budget)
-        print(budget, flush=True)
-        return counted(ctx, F, B, T, v, "budget %d" % budget)
+        ctx.tc_set_option(tc.TC_OPT_PRIORITY_BOOST, boost)
+        print(budget, boost, flush=True)
+        return counted(ctx, F, B, T, v, "budget %d boost %d" % (budget, boost))
     return reads
 
 
@@ -171,3 +172,14 @@ def test_split_budget_is_the_one_set(ctx):
     assert reads(120) > never        # the default: fewer in a launch this small
     for budget in (119, 121, 1 << 20):
         assert reads(budget) == never   # no walk of this view is as long
+
+
+# a wave's priority is raised within the budget, not before it begins
+@pytest.mark.parametrize("queue", [1 << 17, 1500])
+def test_priority_boost_leaves_the_budget(ctx, queue):
+    ctx.tc_set_option(tc.TC_OPT_SPLIT_QUEUE, queue)
+    reads = rough(ctx)
+    never = reads(0)
+    for boost in (3, 9, 1000, 1 << 20):
+        assert reads(20, boost) > never
+        assert reads(1 << 20, boost) == never
