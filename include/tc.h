@@ -288,7 +288,8 @@ tc_status tc_shade_views(tc_context *ctx, const tc_view *views, int32_t n,
                                     steps, so long walks do not trail the
                                     launch (0: never; default 0) */
 #define TC_OPT_SPLIT_BUDGET 11   /* hierarchical mode: a ray still walking
-                                    after this many steps is finished by a
+                                    after this many steps (or up to twice as
+                                    many, if it skims a surface) is finished by a
                                     second pass that walks 64 runs of its
                                     path per wave in parallel (4 waves by
                                     default), each from the exact state the

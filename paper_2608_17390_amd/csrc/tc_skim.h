@@ -447,8 +447,9 @@ __device__ __forceinline__ void skim_step(const skim_ray& f, skim_t& s) {
 }
 
 // The whole walk: its state (kHitCell with the record in word and depth,
-// kMissed, or kWalking when the budget ran out; a ray that passes a cell
-// within the margin of its solid starts the budget anew).  With kBoost a wave
+// kMissed, or kWalking when the budget ran out).  The steps a ray took before it
+// passed a cell within the margin of its solid are not counted: a split pass's
+// budget is halved there, until nothing is left of it.  With kBoost a wave
 // raises its issue priority after boost, 2 boost and 4 boost steps of its walk,
 // of which it has taken `done` before (an instance of its own: the stops cost
 // the walk 1.4 %).
@@ -462,7 +463,7 @@ __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
   float ze = 0.0f;
   const bool down = f.dzl < 0.0f;
   int32_t used = done;
-  const int32_t end = done + budget;
+  int32_t end = done + budget;
   for (;;) {
     int32_t stop = end - used, st;
     if (kBoost && used < 4 * boost)
@@ -488,6 +489,10 @@ __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
     }
     // within the margin of solid, but not in it: on to the next cell
     skim_step(f, s);
+    if (budget <= kIterCap) {
+      end -= (end - used + 1) >> 1;
+      if (end == used) return kWalking;
+    }
   }
 }
 

@@ -183,3 +183,25 @@ def test_priority_boost_leaves_the_budget(ctx, queue):
     for boost in (3, 9, 1000, 1 << 20):
         assert reads(20, boost) > never
         assert reads(1 << 20, boost) == never
+
+
+# steps that fall one height a cell, and rays that fall with them, 20 units
+# above every edge, from so far that the margin covers it: each cell is passed
+# in whole numbers, and the budget still ends
+@pytest.mark.parametrize("boost", [0, 7])
+def test_passed_cells_use_the_budget(ctx, boost):
+    F = np.zeros((64, 640), np.uint8)
+    F[:, :200] = 220 - np.arange(200)
+    F[:, 205:] = 40
+    Z = np.zeros_like(F)
+    load(ctx, F, Z, Z)
+    v = ortho((-2000 * S, 10 * S + 5, 2221 * S + 20), (0, S // 4, 0), (0, 0, 0), (K, 3, -K), 8, 5)
+    ctx.tc_set_option(tc.TC_OPT_BEAM_PASSES, 0)
+    ctx.tc_set_option(tc.TC_OPT_PRIORITY_BOOST, boost)
+    got = {}
+    for budget in (0, 60):
+        ctx.tc_set_option(tc.TC_OPT_SPLIT_BUDGET, budget)
+        print(budget, boost, flush=True)
+        got[budget] = counted(ctx, F, Z, Z, [v], "budget %d" % budget)
+    assert got[0] >= 200          # a cell at a time
+    assert got[60] > got[0], got
