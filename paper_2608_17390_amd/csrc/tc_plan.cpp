@@ -7,7 +7,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <system_error>
 #include <thread>
 
 namespace tci {
@@ -82,7 +81,7 @@ bool columns_valid(const uint8_t* F, const uint8_t* B, const uint8_t* T,
   for (int32_t k = 1; k < n; ++k) {
     try {
       th[k] = std::thread(check, &band[k]);
-    } catch (const std::system_error&) {
+    } catch (...) {   // (std::system_error, or std::bad_alloc for its state)
     }
   }
   for (int32_t k = 0; k < n; ++k)
