@@ -208,7 +208,7 @@ __global__ void edits_kernel(const tci_edit* __restrict__ edits, int32_t n,
 }
 
 // Edits and the six pyramid levels over them in one launch, for lists of at
-// most kTileEdits edits.  A block takes a block of 64 x 64 cells that an
+// most tci::kTileEdits edits.  A block takes a block of 64 x 64 cells that an
 // edit's rectangle touches, a wave 16 x 16 of them, a lane 2 x 2: it applies
 // every edit that covers its cells, in list order, and has the node and mask
 // of level 1 at hand; those of levels 2..4 fold together by cross-lane
@@ -224,7 +224,6 @@ __global__ void edits_kernel(const tci_edit* __restrict__ edits, int32_t n,
 // launches (one for the cells, five for the levels) of 25 us together and is
 // two of 17 (7 this one).  Longer lists than kTileEdits compare too many
 // edits per block of cells and keep the launch per cells and per level group.
-constexpr int32_t kTileEdits = 512;
 constexpr int32_t kTileThreads = 1024;
 
 // The levels' records in LDS: a kernel that goes through the levels in turn
@@ -739,7 +738,7 @@ hipError_t tci_launch_update_window(const tci_map& m, uint32_t* base, int32_t L,
   return hipGetLastError();
 }
 
-bool tci_edit_tiles(int32_t n) { return n <= kTileEdits; }
+bool tci_edit_tiles(int32_t n) { return n <= tci::kTileEdits; }
 
 hipError_t tci_launch_edit_tiles(const tci_map& m, const tci_edit* edits, int32_t n,
                                  const uint8_t* patch, uint32_t* base, int32_t max_w,

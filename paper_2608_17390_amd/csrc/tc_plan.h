@@ -102,6 +102,10 @@ struct tci_edit {
 
 namespace tci {
 
+// Edits up to which a list's cells and the six levels over them are updated
+// in one launch (edit_tiles_kernel).
+constexpr int32_t kTileEdits = 512;
+
 // Bytes of one split queue entry (view, pixel, first line, 0).
 constexpr size_t kQueueEntry = 16;
 
@@ -110,8 +114,8 @@ constexpr size_t kQueueEntry = 16;
 // overlap lists, and SET patch bytes.  Overlap lists: int32 start[n + 1]
 // then the lists, edit i's (the other edits whose clipped rectangle meets
 // its own, ascending) at start[i] .. start[i + 1] - 1 after start[n]; with
-// olap_all set (too many candidates to list) every edit tests every other
-// and the lists are empty.
+// olap_all set (too many candidates to list, or at most kTileEdits edits,
+// whose kernel finds the overlaps itself) the lists are empty.
 struct EditPlan {
   int32_t n = 0;
   int32_t top = 0;
