@@ -224,6 +224,14 @@ __global__ void edits_kernel(const tci_edit* __restrict__ edits, int32_t n,
 // launches (one for the cells, five for the levels) of 25 us together and is
 // two of 17 (7 this one).  Longer lists than kTileEdits compare too many
 // edits per block of cells and keep the launch per cells and per level group.
+// Where many edits meet one block, what bounds it is the way through them, one
+// after the other: their records are held in LDS, the next one's read while
+// one is applied, a wave goes through those that touch its own cells, and
+// nothing of a cell's column is touched on the way.  The last patch over a cell
+// is read at the end, and craters add up: max(max(F - a, 0) - b, 0) is
+// max(F - (a + b), 0).  A frame of 200 craters of 16 cells in 24 x 24: 101 us; with a
+// record read from memory and applied to the column at a time 299, and with the
+// launch per cells 101.  512 of 96 cells in 200 x 200: 305, 604 and 490.
 constexpr int32_t kTileThreads = 1024;
 
 // The levels' records in LDS: a kernel that goes through the levels in turn
@@ -246,8 +254,8 @@ __device__ inline void load_levels_lds(const tci_map& m, levels_t& t) {
 struct clip_t {
   int32_t x0, y0, x1, y1;
 };
-__device__ inline clip_t clip(const tci_edit& e, int32_t W, int32_t H) {
-  return clip_t{max(e.x0, 0), max(e.y0, 0), min(e.x0 + e.w, W) - 1, min(e.y0 + e.h, H) - 1};
+__device__ inline clip_t clip(const int4& e, int32_t W, int32_t H) {
+  return clip_t{max(e.x, 0), max(e.y, 0), min(e.x + e.z, W) - 1, min(e.y + e.w, H) - 1};
 }
 // Does it touch block (bx, by) of 2^sh x 2^sh cells?
 __device__ inline bool touches(const clip_t& r, int32_t bx, int32_t by, int32_t sh) {
@@ -307,19 +315,30 @@ __global__ __launch_bounds__(kTileThreads) void edit_tiles_kernel(
     uint32_t* __restrict__ base) {
   __shared__ levels_t tab;
   __shared__ uint32_t node4[16], lo4[16], hi4[16];
+  // the edits' rectangles (x0, y0, w, h), and what else they are: for a patch
+  // -1 and its bytes' offset, for a crater its depth and 1 / w^2, a little less
+  __shared__ int4 rect[tci::kTileEdits], rest[tci::kTileEdits];
   const int32_t ei = blockIdx.x, lane = threadIdx.x & 63;
   const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const clip_t r = clip(edits[ei], m.W, m.H);
+  auto rect_of = [](const tci_edit& e) { return make_int4(e.x0, e.y0, e.w, e.h); };
+  const clip_t r = clip(rect_of(edits[ei]), m.W, m.H);
   if (r.x0 > r.x1 || r.y0 > r.y1) return;
-  // the first 64 edits' rectangles, one per lane
-  const clip_t mine = clip(edits[min(lane, n - 1)], m.W, m.H);
-  load_levels_lds(m, tab);
   const int32_t bx0 = r.x0 >> 6, by0 = r.y0 >> 6;
   const int32_t nbx = (r.x1 >> 6) - bx0 + 1, nb = nbx * ((r.y1 >> 6) - by0 + 1);
-  // which of edits c .. c + 63 touch the block (all lanes take part)
-  auto who = [&](int32_t c, int32_t bx, int32_t by) {
-    const clip_t q = c == 0 ? mine : clip(edits[min(c + lane, n - 1)], m.W, m.H);
-    return (uint64_t)__ballot(c + lane < n && touches(q, bx, by, 6));
+  if ((int32_t)blockIdx.y >= nb) return;
+  if ((int32_t)threadIdx.x < n) {
+    const tci_edit e = edits[threadIdx.x];
+    rect[threadIdx.x] = rect_of(e);
+    rest[threadIdx.x] = e.kind == kEditSet
+        ? make_int4(-1, 0, (int32_t)e.data_off, (int32_t)(e.data_off >> 32))
+        : make_int4(e.depth, __float_as_int(0x1.fffff8p-1f / (float)(e.w * e.w)), 0, 0);
+  }
+  load_levels_lds(m, tab);
+  // which of edits c .. c + 63 touch block (bx, by) of 2^sh x 2^sh cells (all
+  // lanes take part)
+  auto who = [&](int32_t c, int32_t bx, int32_t by, int32_t sh) {
+    return (uint64_t)__ballot(c + lane < n &&
+                              touches(clip(rect[min(c + lane, n - 1)], m.W, m.H), bx, by, sh));
   };
   // (every wave of the block runs the same rounds: the barriers are reached
   // by all of them)
@@ -338,20 +357,69 @@ __global__ __launch_bounds__(kTileThreads) void edit_tiles_kernel(
     }
     bool owned = true;
     for (int32_t c = 0; c <= ei && owned; c += 64)
-      owned = (who(c, bx, by) & (ei - c < 64 ? (1ull << (ei - c)) - 1 : ~0ull)) == 0;
+      owned = (who(c, bx, by, 6) & (ei - c < 64 ? (1ull << (ei - c)) - 1 : ~0ull)) == 0;
     if (!owned) continue;
+    // per cell: the last patch over it, and of the craters after that what
+    // they take off and whether one is over it (dig > 0)
+    int32_t set[4] = {-1, -1, -1, -1}, dig[4] = {0, 0, 0, 0};
+    uint32_t drop[4] = {0u, 0u, 0u, 0u};
     for (int32_t c = ei & ~63; c < n; c += 64) {
-      uint64_t mask = who(c, bx, by);
+      uint64_t mask = who(c, bx * 4 + (wave & 3), by * 4 + (wave >> 2), 4);
+      if (!mask) continue;
+      int32_t k = c + __ffsll((unsigned long long)mask) - 1;
+      int4 e = rect[k], q = rest[k];
       while (mask) {
-        const int32_t k = c + __ffsll((unsigned long long)mask) - 1;
         mask &= mask - 1;
-        const tci_edit& e = edits[k];
+        const int32_t next = mask ? c + __ffsll((unsigned long long)mask) - 1 : k;
+        const int4 en = rect[next], qn = rest[next];
+        const int32_t i = x - e.x, j = y - e.y;
+        if (__builtin_amdgcn_readfirstlane(q.x) < 0) {
+          const bool ci[2] = {(uint32_t)i < (uint32_t)e.z, (uint32_t)(i + 1) < (uint32_t)e.z};
+          const bool cj[2] = {(uint32_t)j < (uint32_t)e.w, (uint32_t)(j + 1) < (uint32_t)e.w};
 #pragma unroll
-        for (int32_t d = 0; d < 4; ++d) {
-          const int32_t cx = x + (d & 1), cy = y + (d >> 1);
-          uint32_t& col = d & 1 ? p[d >> 1].y : p[d >> 1].x;
-          if (cx < m.W && cy < m.H && covers(e, cx, cy)) col = apply_one(e, patch, col, cx, cy);
+          for (int32_t d = 0; d < 4; ++d) {
+            const bool over = ci[d & 1] & cj[d >> 1];
+            set[d] = over ? k : set[d];
+            drop[d] = over ? 0u : drop[d];
+            dig[d] = over ? 0 : dig[d];
+          }
+        } else {
+          // A cell is in the crater if R2 - r2 > 0 (its rectangle, of side s <=
+          // 4096, touches the wave's cells, so |a| < 2^14).  That is below 2^24,
+          // and times a depth below 2^32; the quotient of it by R2 comes from
+          // the lowered reciprocal, so it is right or one too small.
+          const int32_t a = 2 * i + 1 - e.z, g = 2 * j + 1 - e.z, R2 = __mul24(e.z, e.z);
+          const int32_t aa[2] = {__mul24(a, a), __mul24(a + 2, a + 2)};
+          const int32_t gg[2] = {R2 - __mul24(g, g), R2 - __mul24(g + 2, g + 2)};
+          const float inv = __int_as_float(q.y);
+#pragma unroll
+          for (int32_t d = 0; d < 4; ++d) {
+            const int32_t in2 = gg[d >> 1] - aa[d & 1];
+            dig[d] = max(dig[d], in2);
+            const uint32_t num = __umul24((uint32_t)q.x, (uint32_t)max(in2, 0));
+            const uint32_t t = (uint32_t)((float)num * inv);
+            const uint32_t left = num - __umul24(__umul24(t, (uint32_t)e.z), (uint32_t)e.z);
+            drop[d] += t + (left >= (uint32_t)R2 ? 1u : 0u);
+          }
         }
+        k = next;
+        e = en;
+        q = qn;
+      }
+    }
+#pragma unroll
+    for (int32_t d = 0; d < 4; ++d) {
+      const int32_t cx = x + (d & 1), cy = y + (d >> 1);
+      uint32_t& col = d & 1 ? p[d >> 1].y : p[d >> 1].x;
+      if (cx < m.W && cy < m.H) {
+        if (set[d] >= 0) {
+          const int4 e = rect[set[d]], q = rest[set[d]];
+          const int64_t off = (int64_t)(((uint64_t)(uint32_t)q.w << 32) | (uint32_t)q.z);
+          const int64_t size = (int64_t)e.z * e.w, o = off + (int64_t)(cy - e.y) * e.z + (cx - e.x);
+          col = (uint32_t)patch[o] | (uint32_t)patch[o + size] << 8 | (uint32_t)patch[o + 2 * size] << 16;
+        }
+        const uint32_t F = col & 0xFF;
+        if (dig[d] > 0) col = F > drop[d] ? F - drop[d] : 0u;   // slab removed: B = T = 0
       }
     }
     if (in) {
