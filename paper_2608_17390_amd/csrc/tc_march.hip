@@ -52,7 +52,19 @@ namespace {
 constexpr int32_t kPackets = 2;
 
 constexpr int32_t kGroup = 4;    // samples tested together
-constexpr int32_t kBeam = 6;     // passes of the packet beam
+// Passes of the packet beam, by the march's samples: one costs about as much
+// as three or four samples, and the first finds most of the way.  Eight
+// 1280x800 views at eye level with 8, 16, 32, 64 and 128 samples take 107, 121,
+// 144, 189 and 270 us without it, 129, 144, 164, 200 and 262 with one pass, 138,
+// 151, 165, 192 and 240 with two, 152, 162, 174, 193 and 222 with six; a view
+// from above 34, 40, 52, 75 and 119, 34, 36, 40, 46 and 59, 35, 35, 38, 41 and 49,
+// and 37, 38, 39, 43 and 49.
+// (the last is an instance of its own, kLong: a number of passes that is known
+// is 2 % of its time).
+constexpr int32_t kLongSteps = 96, kBeam = 6;
+__device__ __forceinline__ int32_t beam_passes(int32_t steps) {
+  return steps < 12 ? 0 : steps < 32 ? 1 : 2;
+}
 
 // SOLID on a packed column word (F | B << 8 | T << 16): 0 empty, 1 floor,
 // 2 slab.
@@ -73,7 +85,7 @@ __device__ __forceinline__ void at(const fray& r, float t, float& x, float& y, f
   z = r.oz + t * r.dz;
 }
 
-template <bool kCount>
+template <bool kCount, bool kLong>
 __global__ __launch_bounds__(64 * kPackets) void march_kernel(
     tci_map m, const tci_view* __restrict__ views, int32_t nviews,
     const int64_t* __restrict__ pkt_prefix, int64_t npkt, void* out,
@@ -94,7 +106,9 @@ __global__ __launch_bounds__(64 * kPackets) void march_kernel(
   // the packet's common start (all 64 lanes take part)
   float t_start = 0.0f;
   int32_t unused = 0;
-  if (!kCount) t_start = beam_start(m, lv, woff, v, tx, ty, kBeam, lane, unused) * 0x1p-16f;
+  const int32_t passes = kLong ? kBeam : beam_passes(o.march_steps);
+  if (!kCount && passes > 0)
+    t_start = beam_start(m, lv, woff, v, tx, ty, passes, lane, unused) * 0x1p-16f;
   const int32_t pw = v.pw_log2;
   const int32_t px = (tx << pw) + (lane & ((1 << pw) - 1)), py = (ty << (6 - pw)) + (lane >> pw);
   if (px >= v.w || py >= v.h) return;
@@ -218,7 +232,9 @@ hipError_t tci_launch_march(const tci_map& m, const tci_view* views,
                             hipStream_t s) {
   int64_t blocks = (npkt + kPackets - 1) / kPackets;
   if (blocks < 1) return hipSuccess;
-  auto kern = o.count ? march_kernel<true> : march_kernel<false>;
+  auto kern = o.count                         ? march_kernel<true, true>
+              : o.march_steps >= kLongSteps   ? march_kernel<false, true>
+                                              : march_kernel<false, false>;
   hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(64 * kPackets), 0, s, m,
                      views, nviews, pkt_prefix, npkt, out, o);
   return hipGetLastError();
