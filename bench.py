@@ -21,7 +21,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # the sources of the headline traversal kernels (the committed profiles
 # record their hash)
 RENDER_SRCS = [os.path.join(ROOT, "paper_2608_17390_amd", "csrc", f)
-               for f in ("tc_walk.h", "tc_skim.h", "tc_beam.h", "tc_packet.h", "tc_render.hip")]
+               for f in ("tc_walk.h", "tc_corner.h", "tc_skim.h", "tc_beam.h", "tc_packet.h",
+                         "tc_render.hip")]
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
@@ -316,12 +317,11 @@ def march_protocol(torch, tc, synth, steps, warmup):
             "march_grays_per_s": n / (np.mean(times["march"]) * 1e-3) / 1e9,
             "exact_grays_per_s": n / (np.mean(times["hier"]) * 1e-3) / 1e9,
             "samples_per_ray": samples / (n * len(views)),
-            "march_roofline": {"bound": "hbm", "achieved": alg / (kms * 1e-3) / 1e9,
-                               "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                               "frac": alg / (kms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-                               "alg_bytes_per_view": alg / len(views),
-                               "kernel_ms_per_view": kms / len(views)},
-            "shade_roofline": {"bound": "hbm", "achieved": shade_alg / (shade_ms * 1e-3) / 1e9,
+            # (the method's bytes: its samples before a packet's common start are in
+            # this count and not read, so no rate of the kernel follows from it)
+            "march_kernel": {"bound": "valu_issue", "method_bytes_per_view": alg / len(views),
+                             "kernel_ms_per_view": kms / len(views)},
+            "shade_roofline": {"bound": "longest shadow walks", "achieved": shade_alg / (shade_ms * 1e-3) / 1e9,
                                "peak": PEAK_HBM_GBS, "unit": "GB/s",
                                "frac": shade_alg / (shade_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
                                "alg_bytes_per_view": shade_alg,
@@ -662,13 +662,19 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "int64",
+        # (the walk, and what decides the steps and cells that its rounding leaves open)
+        "dtype": "fp32+int64",
         "data": "synthetic",
         "config": {"workload": "c2: 2048x2048 two-layer map (30% two-layer cells, "
                                "40-unit cliffs), one 1920x1080 eye-level horizon view",
                    "rays_per_frame": rays, "render_mode": args.mode, "beam_passes": beam,
                    "frame_ms_median": med, "frame_ms_p99": float(np.percentile(ms, 99))},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS,
+        # achieved and peak are algorithmic bytes and HBM's; what binds is the issue of
+        # vector instructions (the counters' verdict: HBM moves a fifth of the algorithmic
+        # bytes, far below peak; a VALU instruction of the walk's mix takes 3.0 to 3.2 cycles
+        # of its SIMD, so issue binds while the launch is full, and its longest walks in
+        # the rest)
+        "roofline": {"bound": "valu_issue", "achieved": achieved, "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": achieved / PEAK_HBM_GBS,
                      # HBM bytes per traversal (FETCH_SIZE + WRITE_SIZE, copy-calibrated)
                      "traffic": traffic,
@@ -686,11 +692,6 @@ def main():
                      # (SQ_BUSY_CYCLES over 32 engines x GRBM_GUI_ACTIVE per XCD)
                      "sq_busy_frac": profile_value(RENDER_SRCS, "render_c2_counters",
                                                    "sq_busy_frac"),
-                     # the counters' verdict: HBM moves a fifth of the algorithmic bytes, far
-                     # below peak; a VALU instruction of the walk's mix takes 3.0 to 3.2 cycles
-                     # of its SIMD, so issue binds while the launch is full (four fifths of
-                     # the time), and its longest walks in the rest
-                     "binding_roof": "valu_issue",
                      "kernel": KERNEL_NAMES[args.mode],
                      "alg_bytes_per_launch": alg_bytes,
                      "kernel_ms_avg": kavg,

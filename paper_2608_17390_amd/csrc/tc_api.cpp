@@ -265,7 +265,8 @@ namespace {
 // with any budget where walks are short; where they are long 37 + 4, 24 + 8
 // and 19 + 19 us at 120, 48 and 32 steps.  Seven edits with a 640x480 view
 // each: 691, 619, 638 us in all at 120, 64 and 48, seven 320x240 views 239,
-// 239 and 221.  1920x1080 views: 127 + 22 us at 120, 101 + 98 at 48.
+// 239 and 221: 64 suits the larger, 48 the smaller by more.  1920x1080 views,
+// beyond the line: 127 + 22 us at 120, 101 + 98 at 48.
 constexpr int32_t kSmallBudget = 48;
 int32_t split_budget(const tc_context* ctx, const ViewPlan& p, int32_t waves) {
   return ctx->split_budget == kSplitBudget && p.npkt <= (int64_t)ctx->num_cu * 4 * waves

@@ -1,8 +1,10 @@
 // Ray casting kernels: one thread per pixel over 8x8 pixel packets, the
 // split pass for the longest walks, and persistent packet-queue waves.  The
-// walk itself (tc_walk.h) is the exact cell sequence of a 2D digital
-// differential analyser over the map, accelerated by the per-layer min/max
-// pyramid (Section 3.1 SOLID and RAYMARCH, Section 3.2 skip-to-exit).
+// walk is the exact cell sequence of a 2D digital differential analyser over
+// the map, accelerated by the per-layer min/max pyramid (Section 3.1 SOLID and
+// RAYMARCH, Section 3.2 skip-to-exit): in single precision with exact decisions
+// (tc_skim.h), and in whole numbers throughout (tc_walk.h) in the flat and
+// persistent modes and the split pass's short queues.
 #include <hip/hip_ext.h>
 
 #include "tc_beam.h"

@@ -9,7 +9,8 @@
 // all the time.  Measured, the render of the exact walk before and of this
 // one after (MI355X): 64 mixed views and 8 shadow passes 4.69 -> 3.72 ms,
 // twelve 1280x800 views 417 -> 346 us, a 1920x1080 horizon view 210 -> 173
-// us.
+// us, when it came in; 4.62 -> 3.35 ms, 398 -> 316 us and 101 -> 74 us (another
+// such view) as it stands.
 //
 // A step of the exact walk spends most of its instructions on 48-bit
 // products: two crossing keys, an exit height and three scaled heights to
@@ -260,7 +261,8 @@ __device__ __forceinline__ void load_voxel_levels(const tci_voxels& vx, uint4* r
 // 3.2) instead: a node of level L >= the voxels' footprint level Lv is voxel
 // column (ni, nj) of voxel level L - Lv; nodes below Lv are always descended
 // (the leaf voxel's cells are then tested one by one), and a climb from below
-// Lv goes straight to Lv, when the step left the leaf voxel.
+// Lv goes straight to Lv, when the step entered a new parent of the leaf
+// voxel: its up to three siblings under the same parent are walked on cells.
 enum { kMinMax = 0, kMasks = 1, kVoxels = 2 };
 struct skim_test {
   const uint32_t* moff;
@@ -365,11 +367,11 @@ __device__ __forceinline__ int32_t skim_steps(const tci_map& m, const lvl_t* lv,
       s.y = y;
       s.zin = zn;
     }
-    // (the one place a lane leaves a step through: with a return in each branch
-    // a step copied some ten registers; 64 mixed views and 8 shadow passes
-    // 3.55 -> 3.42 ms, twelve 1280x800 views 336 -> 327 us, a 320x240 view
-    // 33.6 -> 31.5, a 1280x800 view shaded 121.5 -> 115.2, two cave views 142
-    // -> 131)
+    // (the one place a lane leaves a step through, against a return in each
+    // branch: 64 mixed views and 8 shadow passes 3.55 -> 3.42 ms, twelve 1280x800
+    // views 336 -> 327 us, a 320x240 view 33.6 -> 31.5, a 1280x800 view shaded
+    // 121.5 -> 115.2, two cave views 142 -> 131; a headline wave issues 601
+    // scalar instructions then, 714 before, and 12 vector ones more)
     if (st != kWalking) break;
   }
   if (st == kHitCell) s.L = 0;

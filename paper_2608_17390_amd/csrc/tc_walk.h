@@ -1,4 +1,7 @@
-// The exact cell walk, shared by the render kernels and the shading pass.
+// The exact cell walk in whole numbers: the flat and persistent modes and the
+// split pass's short queues walk this way; the single-precision walk of
+// tc_skim.h, which the other modes and the shadow rays use, decides the cells
+// that its rounding leaves open with the same quantities.
 //
 // Each pixel's ray walks the exact cell sequence of a 2D digital
 // differential analyser over the map (the exact limit of the paper's
@@ -350,11 +353,12 @@ __device__ __forceinline__ void walk_at_origin(const ray_t& r, int32_t L0, walk_
 // Depth of a hit at time tn / td (units over a direction component, both
 // whole; td > 0) of a ray of direction (dx, dy, dz), whole numbers: |tn / td|
 // times the direction's length, in double precision, rounded once.  The
-// quotient and the root come from the hardware's estimates and Newton
-// steps, within about one unit in the double's last place; the general
-// division and square root, which also handle ranges that whole numbers
-// below 2^48 do not reach, take twenty more instructions (1.4 % of the
-// headline frame).
+// quotient and the root come from the hardware's estimates and Newton steps,
+// which end with the residual of the rounded value: they round as the general
+// division and square root do (8e8 quotients and roots of such whole numbers,
+// with estimates off by up to 2^-23, differ in none).
+// Those also handle ranges that whole numbers below 2^48 do not reach, with
+// twenty more instructions (1.4 % of the headline frame).
 __device__ __forceinline__ float hit_depth(double tn, double td, double dx, double dy,
                                            double dz) {
   const double l2 = fma(dx, dx, fma(dy, dy, dz * dz));   // exact: below 2^48
