@@ -71,8 +71,8 @@ __device__ __forceinline__ double recip(int64_t b) {
 }
 
 // Does a ray from P along L meet any solid (the single-precision walk of
-// tc_skim.h)?  `reads` gains the nodes and cells the walk read.  kDir: the sign of L[2] (1 negative, 2 otherwise),
-// the walk loop's specialisation.
+// tc_skim.h)?  `reads` gains the nodes and cells the walk read.  kDir: the sign
+// of L[2] (1 negative, 2 otherwise), the walk loop's specialisation.
 template <int kDir, bool kCount>
 __device__ __forceinline__ bool occluded(const tci_map& m, const lvl_t* lv, const int64_t P[3],
                                          const int32_t L[3], int32_t Lmax,
@@ -108,7 +108,8 @@ __device__ __forceinline__ bool occluded(const tci_map& m, const lvl_t* lv, cons
 // SIMD, against 3 in the render), so what pays is a shorter step: one
 // 1280x800 view 60 -> 54 us (and 75 -> 66 where more rays are long) with
 // the single-precision walk, the light's unit vector from the host and one
-// reciprocal for the hit point.
+// reciprocal for the hit point; twelve such views 58.9 us each with one margin
+// for all heights of the walk, 48.7 with the one that follows the ray's.
 template <int kDir, bool kCount>
 __global__ __launch_bounds__(64 * kPackets) void shade_kernel(
     tci_map m, const tci_view* __restrict__ views, int32_t nviews,

@@ -499,9 +499,9 @@ __device__ __forceinline__ int32_t skim_walk(const tci_map& m, const lvl_t* lv,
 }
 
 // Does the ray (its integers in q) meet any solid?  Its origin usually lies
-// a unit off a surface, far inside the margin, so in the origin's cell the
-// entry is compared in whole numbers and the exit alone with the margin;
-// the walk proper begins in the next cell.  A walk that uses up its bound
+// a unit off a surface, so in the origin's cell the entry is compared in whole
+// numbers and the exit alone with the margin; the walk proper begins in the
+// next cell.  A walk that uses up its bound
 // (never expected) counts as a hit.
 template <int kDir, bool kCount>
 __device__ __forceinline__ bool skim_blocked(const tci_map& m, const lvl_t* lv, const skim_int& q,
