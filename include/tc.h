@@ -223,7 +223,7 @@ typedef struct tc_shade_params {
 /* Shade n views whose hit records (tc_render_views of the same views on the
  * current map, in any exact render mode) are in hits_device, into
  * rgba_device (one uint32 per pixel, same order), owned by the caller.
- * The shadow rays use the exact walk and the context's render knobs.
+ * The shadow rays use the exact walk (TC_OPT_MAX_LEVEL is its only knob).
  * Errors: as tc_render_views for the views; TC_INVALID_ARG for null
  * pointers, a zero or too long light direction, fog_far <= 0 or not
  * finite, ambient terms outside 0..1. */
