@@ -87,7 +87,9 @@ __device__ __forceinline__ bool beam_box_solid(const tci_map& m, const lvl_t* lv
 
 // Parameter t >= 0 such that no ray of the packet whose tile is (tx, ty)
 // meets solid during [0, t].  Called by all 64 lanes of the wave together
-// (it uses ballots); `reads` gains the nodes this lane read.
+// (it uses ballots); `reads` gains the nodes this lane read.  kPasses > 0: as
+// many passes, whatever `passes` says.
+template <int32_t kPasses = 0>
 __device__ __forceinline__ float beam_start(const tci_map& m, const lvl_t* lv,
                                             const uint32_t* woff, const tci_view& v,
                                             int32_t tx, int32_t ty, int32_t passes,
@@ -147,7 +149,7 @@ __device__ __forceinline__ float beam_start(const tci_map& m, const lvl_t* lv,
   const float g1 = (__builtin_amdgcn_exp2f((float)(lane + 1) * kBeamLog2Growth) - 1.0f) *
                    (1.0f / kBeamGrowth);
   float ta = 0.0f;
-  for (int32_t pass = 0; pass < passes; ++pass) {
+  for (int32_t pass = 0; pass < (kPasses > 0 ? kPasses : passes); ++pass) {
     const float t0 = fmaf(u, g0, ta), t1 = fmaf(u, g1, ta), dt = t1 - t0;
     float lo[3], hi[3];
 #pragma unroll

@@ -59,8 +59,8 @@ constexpr int32_t kGroup = 4;    // samples tested together
 // 151, 165, 192 and 240 with two, 152, 162, 174, 193 and 222 with six; a view
 // from above 34, 40, 52, 75 and 119, 34, 36, 40, 46 and 59, 35, 35, 38, 41 and 49,
 // and 37, 38, 39, 43 and 49.
-// (the last is an instance of its own, kLong: a number of passes that is known
-// is 2 % of its time).
+// The last is an instance of its own, kLong: with a number of passes that is
+// known its passes are unrolled, which is 1 to 2 % of its time.
 constexpr int32_t kLongSteps = 96, kBeam = 6;
 __device__ __forceinline__ int32_t beam_passes(int32_t steps) {
   return steps < 12 ? 0 : steps < 32 ? 1 : 2;
@@ -106,9 +106,12 @@ __global__ __launch_bounds__(64 * kPackets) void march_kernel(
   // the packet's common start (all 64 lanes take part)
   float t_start = 0.0f;
   int32_t unused = 0;
-  const int32_t passes = kLong ? kBeam : beam_passes(o.march_steps);
-  if (!kCount && passes > 0)
-    t_start = beam_start(m, lv, woff, v, tx, ty, passes, lane, unused) * 0x1p-16f;
+  if constexpr (!kCount && kLong) {
+    t_start = beam_start<kBeam>(m, lv, woff, v, tx, ty, kBeam, lane, unused) * 0x1p-16f;
+  } else if constexpr (!kCount) {
+    const int32_t passes = beam_passes(o.march_steps);
+    if (passes > 0) t_start = beam_start(m, lv, woff, v, tx, ty, passes, lane, unused) * 0x1p-16f;
+  }
   const int32_t pw = v.pw_log2;
   const int32_t px = (tx << pw) + (lane & ((1 << pw) - 1)), py = (ty << (6 - pw)) + (lane >> pw);
   if (px >= v.w || py >= v.h) return;
